@@ -1,7 +1,8 @@
 // One (replica type, stats, reset) slice of the INT8-codec round kernels, for
-// every K.  Compiled once per slice with -DAL_RT=<0|1> -DAL_RTNAME=<f32|bf16>
+// every K (up to 8 workers int8_round_kernel, above int8_wide_kernel).  Compiled once per slice with -DAL_RT=<0|1> -DAL_RTNAME=<f32|bf16>
 // -DAL_STATS=<0|1> -DAL_RESET=<0|1>.
 #include "int8_kernels.hpp"
+#include "int8_wide_kernels.hpp"
 
 #if !defined(AL_RT) || !defined(AL_RTNAME) || !defined(AL_STATS) || !defined(AL_RESET)
 #error "AL_RT, AL_RTNAME, AL_STATS and AL_RESET must be defined"
@@ -15,17 +16,23 @@ namespace autoloco {
 namespace {
 
 template <int K>
+constexpr auto kernel_of() {
+    if constexpr (K <= 8)
+        return &int8_round_kernel<K, AL_RT, AL_STATS != 0, AL_RESET != 0>;
+    else
+        return &int8_wide_kernel<K, AL_RT, AL_STATS != 0, AL_RESET != 0>;
+}
+
+template <int K>
 hipError_t launch_k(int blocks, hipStream_t stream, const Int8Args& a) {
-    hipLaunchKernelGGL((int8_round_kernel<K, AL_RT, AL_STATS != 0, AL_RESET != 0>), dim3(blocks), dim3(kInt8Threads),
-                       0, stream, a);
+    hipLaunchKernelGGL(kernel_of<K>(), dim3(blocks), dim3(kInt8Threads), 0, stream, a);
     return hipGetLastError();
 }
 
 template <int K>
 int occ_k() {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, int8_round_kernel<K, AL_RT, AL_STATS != 0, AL_RESET != 0>,
-                                                     kInt8Threads, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel_of<K>(), kInt8Threads, 0) != hipSuccess)
         return 0;
     return b;
 }

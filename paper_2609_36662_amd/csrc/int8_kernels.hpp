@@ -97,13 +97,18 @@ __device__ __forceinline__ uint32_t wave_max_bits(uint32_t x) {
     return max(a, b);
 }
 
+// Workgroup barrier that waits for this wave's LDS traffic only.  __syncthreads
+// would also wait for every direct global-to-LDS load in flight, which the
+// prefetch of the next block is.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Maximum of NV non-negative values over the workgroup (every thread gets the
 // result).  One barrier: the caller gives each use within a loop iteration its
 // own LDS region, so a wave that runs ahead into the next iteration writes a
 // region every other wave has finished reading (they all passed a later
 // barrier of this iteration after reading it).  Every thread of the workgroup
 // must be active.
-template <int NV, int NT>
+template <int NV, int NT, bool LB = false>
 __device__ __forceinline__ void block_max(float (&v)[NV], uint32_t* lds) {
     constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63;
@@ -113,7 +118,7 @@ __device__ __forceinline__ void block_max(float (&v)[NV], uint32_t* lds) {
         const uint32_t m = wave_max_bits(__float_as_uint(v[j]));
         if (lane == 0) lds[j * NW + wave] = m;
     }
-    __syncthreads();
+    if constexpr (LB) lds_barrier(); else __syncthreads();
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         uint32_t x = lds[j * NW];
@@ -135,14 +140,12 @@ __device__ __forceinline__ void block_max(float (&v)[NV], uint32_t* lds) {
 // order, so the 8 workers' reads fall in distinct banks).  The same reuse rule
 // as block_max holds for the LDS region.
 constexpr int kWorkerMaxStride(int nw) { return 4 * nw + 4; }
-template <int K, int NW>
-__device__ __forceinline__ float worker_block_max(const float (&v)[K], uint32_t* lds) {
-    static_assert(K <= 8, "at most 8 workers");
+
+// Stores this wave's 4 row maxima of each of 8 workers.
+template <int NW>
+__device__ __forceinline__ void worker_max_rows(const uint32_t (&m)[8], uint32_t* lds) {
     constexpr int S = kWorkerMaxStride(NW);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t m[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) m[j] = j < K ? __float_as_uint(v[j]) : 0u;
     const bool lo = (lane & 4) == 0, even = (lane & 1) == 0, b1 = (lane & 2) != 0;
     uint32_t a4[4], a2[2];
 #pragma unroll
@@ -163,8 +166,37 @@ __device__ __forceinline__ float worker_block_max(const float (&v)[K], uint32_t*
     c = max(c, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0x128, 0xF, 0xF, false));   // row_ror:8
     const int w = (lane & 4) + ((lane & 1) << 1) + ((lane & 2) >> 1);
     if ((lane & 8) == 0) lds[w * S + wave * 4 + (lane >> 4)] = c;
+}
+
+template <int K, int NW>
+__device__ __forceinline__ float worker_block_max(const float (&v)[K], uint32_t* lds) {
+    static_assert(K <= 8, "at most 8 workers");
+    uint32_t m[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) m[j] = j < K ? __float_as_uint(v[j]) : 0u;
+    worker_max_rows<NW>(m, lds);
     __syncthreads();
-    const uint32_t* p = lds + (lane & 7) * S;
+    const uint32_t* p = lds + (threadIdx.x & 7) * kWorkerMaxStride(NW);
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * NW; ++i) r = max(r, p[i]);
+    return __uint_as_float(r);
+}
+
+// The same for 16 workers in two groups of 8, with one barrier: every lane gets
+// worker (lane mod 16)'s maximum.
+template <int NW>
+__device__ __forceinline__ float worker_block_max16(const float (&v)[16], uint32_t* lds) {
+    constexpr int S = kWorkerMaxStride(NW);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t m[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) m[j] = __float_as_uint(v[8 * h + j]);
+        worker_max_rows<NW>(m, lds + h * 8 * S);
+    }
+    lds_barrier();
+    const uint32_t* p = lds + (threadIdx.x & 15) * S;
     uint32_t r = 0;
 #pragma unroll
     for (int i = 0; i < 4 * NW; ++i) r = max(r, p[i]);
@@ -180,37 +212,39 @@ struct BoolC {
     static constexpr bool value = B;
 };
 
-// Each thread of a workgroup owns 8 parameters of a codec block: two runs of
+// Up to 8 workers (above, int8_wide_kernel: K * 8 pseudo-gradients a thread leave
+// no registers for this kernel's way).  Each thread of a workgroup owns 8 parameters of a codec block: two runs of
 // 4, 2,048 apart, so every wavefront instruction covers one contiguous run
 // (1 KB of fp32, 512 B of bf16) and no cache line is written in parts.  The loop runs over the full blocks, in which
 // every load and store is a whole vector; the one shorter last block, if any,
 // goes through a second instance of the same body with per-element accesses.
 // The next block of a workgroup is loaded while the current one is encoded:
-// up to 8 bf16 workers its raw replica words, theta and momentum go to
+// with bf16 replicas its raw replica words, theta and momentum go to
 // registers (the block barriers wait for LDS traffic only), pseudo-gradients
 // are formed from the raw words where they are used, and each thread's fp64
 // sums live in LDS slots of its own, which leaves the registers for it;
-// up to 8 fp32 workers its theta and replica vectors go straight to LDS
+// with fp32 replicas its theta and replica vectors go straight to LDS
 // (global_load_lds_dwordx4, no registers), each wave into pieces only it reads
 // back, behind an explicit count of the vector memory instructions issued
 // after them (the compiler does not order these loads against later LDS
 // reads by itself).
 template <int K, int RT, bool STATS, bool RESET>
 __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
+    static_assert(K <= 8, "up to 8 workers");
     constexpr int NT = kInt8Threads;
     constexpr int V = 8;
     constexpr int NS = STATS ? 2 * K + 1 : 1;
     constexpr int G = 2;   // runs of W parameters per thread
     constexpr int W = V / G;
-    constexpr bool PF = RT == RT_BF16 && K <= 8;
-    // fp32 replicas up to 8 workers: the next block's theta and replica vectors
+    constexpr bool PF = RT == RT_BF16;
+    // fp32 replicas: the next block's theta and replica vectors
     // stream into LDS (direct global-to-LDS loads, no registers) while the
     // current block is encoded; (K + 1) * 16 KB of LDS
-    constexpr bool LP = RT == RT_F32 && K <= 8;
+    constexpr bool LP = RT == RT_F32;
     constexpr int NW = NT / 64;
     constexpr int KW = RT == RT_BF16 ? K : 1;   // raw bf16 replica words held per thread
     // worker block maxima
-    __shared__ uint32_t lds_max[K <= 8 ? 8 * kWorkerMaxStride(NT / 64) : NT / 64 * K];
+    __shared__ uint32_t lds_max[8 * kWorkerMaxStride(NT / 64)];
     __shared__ uint32_t lds_mmax[NT / 64];      // the mean's block maximum
     // prefetched vectors, [stream (theta, replica 0..K-1)][run][wave][lane];
     // every wave reads back only the 1 KB pieces it loaded itself
@@ -438,24 +472,13 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
             for (int e = 0; e < V; ++e) m = fmaxf(m, fabsf(D(k, e)));
             amax[k] = m;
         }
-        float am_lane = 0.0f;   // up to 8 workers: worker (lane mod 8)'s block maximum
-        if constexpr (K <= 8)
-            am_lane = worker_block_max<K, NT / 64>(amax, lds_max);
-        else
-            block_max<K, NT>(amax, lds_max);
+        const float am = worker_block_max<K, NT / 64>(amax, lds_max);   // worker (lane mod 8)'s
 
         // The K scales and their reciprocals are the same in every lane: lane k
         // computes worker k's (one IEEE division of each kind for all workers
         // instead of K), and every lane reads them back.
         float scale_k[K], recip_k[K];
         {
-            const int lane = threadIdx.x & 63;
-            float am = am_lane;
-            if constexpr (K > 8) {
-                am = amax[0];
-#pragma unroll
-                for (int k = 1; k < K; ++k) am = lane == k ? amax[k] : am;
-            }
             const float sv = codec_scale(am);
             const float rv = 1.0f / sv;
 #pragma unroll
