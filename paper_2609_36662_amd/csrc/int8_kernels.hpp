@@ -102,43 +102,36 @@ __device__ __forceinline__ uint32_t wave_max_bits(uint32_t x) {
 // prefetch of the next block is.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Maximum of NV non-negative values over the workgroup (every thread gets the
-// result).  One barrier: the caller gives each use within a loop iteration its
-// own LDS region, so a wave that runs ahead into the next iteration writes a
-// region every other wave has finished reading (they all passed a later
-// barrier of this iteration after reading it).  Every thread of the workgroup
-// must be active.
-template <int NV, int NT, bool LB = false>
-__device__ __forceinline__ void block_max(float (&v)[NV], uint32_t* lds) {
+// Maximum of a non-negative value over the workgroup (every thread gets it).
+// One barrier: the caller gives each use within a loop iteration its own LDS
+// region, so a wave that runs ahead into the next iteration writes a region
+// every other wave has finished reading (they all passed a later barrier of
+// this iteration after reading it).  Every thread of the workgroup must be
+// active.
+template <int NT>
+__device__ __forceinline__ void block_max(float& v, uint32_t* lds) {
     constexpr int NW = NT / 64;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const uint32_t m = wave_max_bits(__float_as_uint(v));
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
+    lds_barrier();
+    uint32_t x = lds[0];
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const uint32_t m = wave_max_bits(__float_as_uint(v[j]));
-        if (lane == 0) lds[j * NW + wave] = m;
-    }
-    if constexpr (LB) lds_barrier(); else __syncthreads();
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        uint32_t x = lds[j * NW];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) x = max(x, lds[j * NW + w]);
-        v[j] = __uint_as_float(x);
-    }
+    for (int w = 1; w < NW; ++w) x = max(x, lds[w]);
+    v = __uint_as_float(x);
 }
 
-// Block maxima of up to 8 workers' non-negative values (compared as their bit
-// patterns) over a workgroup of NW waves; returns worker (lane mod 8)'s in
-// every lane.  Instead of one wavefront reduction per worker, a halving
-// exchange inside each group of 8 lanes (partners 7 - i, i ^ 1, i ^ 2; every
-// lane sends the half of its values its partner keeps) leaves lane i with the
-// group's maximum of worker w(i) = 4 b2 + 2 b0 + b1 (b_j the bits of i), a
-// rotation by 8 lanes joins the two groups of each row of 16, and every wave
-// stores its 4 row values per worker.  After the one barrier each lane reads
-// the 4 NW values of its worker (rows 16-byte aligned, 4 words apart in bank
-// order, so the 8 workers' reads fall in distinct banks).  The same reuse rule
-// as block_max holds for the LDS region.
+// Block maxima of up to 16 workers' non-negative values (compared as their bit
+// patterns) over a workgroup of NW waves, in groups of 8 workers; returns
+// worker (lane mod 8)'s in every lane, or above 8 workers (lane mod 16)'s.
+// Instead of one wavefront reduction per worker, a halving exchange inside each
+// group of 8 lanes (partners 7 - i, i ^ 1, i ^ 2; every lane sends the half of
+// its values its partner keeps) leaves lane i with the group's maximum of worker
+// w(i) = 4 b2 + 2 b0 + b1 (b_j the bits of i), a rotation by 8 lanes joins the
+// two groups of each row of 16, and every wave stores its 4 row values per
+// worker.  After the one barrier each lane reads the 4 NW values of its worker
+// (rows 16-byte aligned, 4 words apart in bank order, so the 8 workers' reads
+// fall in distinct banks).  The same reuse rule as block_max holds for the LDS
+// region.
 constexpr int kWorkerMaxStride(int nw) { return 4 * nw + 4; }
 
 // Stores this wave's 4 row maxima of each of 8 workers.
@@ -170,33 +163,17 @@ __device__ __forceinline__ void worker_max_rows(const uint32_t (&m)[8], uint32_t
 
 template <int K, int NW>
 __device__ __forceinline__ float worker_block_max(const float (&v)[K], uint32_t* lds) {
-    static_assert(K <= 8, "at most 8 workers");
-    uint32_t m[8];
+    static_assert(K <= 16, "at most 16 workers");
+    constexpr int S = kWorkerMaxStride(NW), H = K <= 8 ? 1 : 2;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) m[j] = j < K ? __float_as_uint(v[j]) : 0u;
-    worker_max_rows<NW>(m, lds);
-    __syncthreads();
-    const uint32_t* p = lds + (threadIdx.x & 7) * kWorkerMaxStride(NW);
-    uint32_t r = 0;
-#pragma unroll
-    for (int i = 0; i < 4 * NW; ++i) r = max(r, p[i]);
-    return __uint_as_float(r);
-}
-
-// The same for 16 workers in two groups of 8, with one barrier: every lane gets
-// worker (lane mod 16)'s maximum.
-template <int NW>
-__device__ __forceinline__ float worker_block_max16(const float (&v)[16], uint32_t* lds) {
-    constexpr int S = kWorkerMaxStride(NW);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < H; ++h) {
         uint32_t m[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) m[j] = __float_as_uint(v[8 * h + j]);
+        for (int j = 0; j < 8; ++j) m[j] = 8 * h + j < K ? __float_as_uint(v[8 * h + j < K ? 8 * h + j : 0]) : 0u;
         worker_max_rows<NW>(m, lds + h * 8 * S);
     }
     lds_barrier();
-    const uint32_t* p = lds + (threadIdx.x & 15) * S;
+    const uint32_t* p = lds + (threadIdx.x & (8 * H - 1)) * S;
     uint32_t r = 0;
 #pragma unroll
     for (int i = 0; i < 4 * NW; ++i) r = max(r, p[i]);
@@ -212,281 +189,247 @@ struct BoolC {
     static constexpr bool value = B;
 };
 
-// Up to 8 workers (above, int8_wide_kernel: K * 8 pseudo-gradients a thread leave
-// no registers for this kernel's way).  Each thread of a workgroup owns 8 parameters of a codec block: two runs of
+// Adds x[0..3] to four fp64 sums over all lanes, in one fp64 accumulator a lane:
+// lane i keeps sum i mod 4, adding the four values of its quad (two exchanges:
+// partners i ^ 1, then i ^ 2).
+__device__ __forceinline__ void quad_add(double& acc, float x0, float x1, float x2, float x3) {
+    const bool odd = (threadIdx.x & 1) != 0, hi = (threadIdx.x & 2) != 0;
+    auto pair = [&](float a, float b) {
+        const float send = odd ? a : b, keep = odd ? b : a;
+        return (double)keep + (double)__int_as_float(__builtin_amdgcn_update_dpp(
+                                  0, __float_as_int(send), 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
+    };
+    const double p = pair(x0, x1), q = pair(x2, x3);
+    const uint64_t send = __builtin_bit_cast(uint64_t, hi ? p : q);
+    const uint32_t lo32 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)send, 0x4E, 0xF, 0xF, false);
+    const uint32_t hi32 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(send >> 32), 0x4E, 0xF, 0xF, false);
+    acc += (hi ? q : p) + __builtin_bit_cast(double, (uint64_t)hi32 << 32 | lo32);   // quad_perm 2,3,0,1
+}
+
+// Each thread of a workgroup owns 8 parameters of a codec block: two runs of
 // 4, 2,048 apart, so every wavefront instruction covers one contiguous run
-// (1 KB of fp32, 512 B of bf16) and no cache line is written in parts.  The loop runs over the full blocks, in which
-// every load and store is a whole vector; the one shorter last block, if any,
-// goes through a second instance of the same body with per-element accesses.
-// The next block of a workgroup is loaded while the current one is encoded:
-// with bf16 replicas its raw replica words, theta and momentum go to
-// registers (the block barriers wait for LDS traffic only), pseudo-gradients
-// are formed from the raw words where they are used, and each thread's fp64
-// sums live in LDS slots of its own, which leaves the registers for it;
-// with fp32 replicas its theta and replica vectors go straight to LDS
-// (global_load_lds_dwordx4, no registers), each wave into pieces only it reads
-// back, behind an explicit count of the vector memory instructions issued
-// after them (the compiler does not order these loads against later LDS
-// reads by itself).
+// (1 KB of fp32, 512 B of bf16) and no cache line is written in parts.  The loop
+// runs over the full blocks, in which every load and store is a whole vector;
+// the one shorter last block, if any, goes through a second instance of the same
+// body with per-element accesses.
+//
+// The K pseudo-gradients of a block are used three times with a workgroup barrier
+// between the uses (local energy and block maxima; codes; deviations from the
+// aggregate), so they have to stay on the chip: K * 16 KB, 256 KB at K = 16.  They
+// live in registers, K * 8 of the 256 a thread of an 8-wave workgroup may use, and
+// the rest is arranged around that:
+//   - the next block comes in while this one is encoded, theta and the replicas
+//     by direct global-to-LDS loads (no registers; each wave into pieces only it
+//     reads back, behind an explicit count of the vector memory instructions
+//     issued after them, since the compiler does not order these loads against
+//     later LDS reads by itself), fp32 workers 9 and up into the registers that
+//     the deviations have just freed;
+//   - the block barriers wait for LDS traffic only, not for those loads;
+//   - a thread keeps one fp64 accumulator for four sums (quad_add);
+//   - above 8 workers theta leaves the registers while the codes are formed and is
+//     read from its LDS piece again for the update.
+// Bound by HBM traffic as the round is, at one workgroup a CU.  Kernel time, plain
+// torch allocations, caches flushed, against the kernel before it (the next block
+// of bf16 replicas in registers and fp64 sums in LDS; fp32's in LDS, but waited
+// for at the first barrier and without the non-temporal hint; no prefetch and
+// 1.1 KB of scratch a thread at K = 16):
+//   GPT-2 small, K = 16 fp32, encoded mean (18.0 GB): 3.3-3.6 ms from 8.2-8.9 ms
+//   100M, K = 8 fp32 (8.0 GB): 1.55 ms from 1.67; without the reset 0.81 from 0.91
+//   100M, K = 8 bf16 (4.8 GB): 0.93 ms alike; without the reset 0.575 from 0.625
+//   8M, K = 8 fp32 / bf16: 146 / 95 us from 171 / 104
 template <int K, int RT, bool STATS, bool RESET>
 __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
-    static_assert(K <= 8, "up to 8 workers");
     constexpr int NT = kInt8Threads;
-    constexpr int V = 8;
-    constexpr int NS = STATS ? 2 * K + 1 : 1;
-    constexpr int G = 2;   // runs of W parameters per thread
-    constexpr int W = V / G;
-    constexpr bool PF = RT == RT_BF16;
-    // fp32 replicas: the next block's theta and replica vectors
-    // stream into LDS (direct global-to-LDS loads, no registers) while the
-    // current block is encoded; (K + 1) * 16 KB of LDS
-    constexpr bool LP = RT == RT_F32;
     constexpr int NW = NT / 64;
-    constexpr int KW = RT == RT_BF16 ? K : 1;   // raw bf16 replica words held per thread
-    // worker block maxima
-    __shared__ uint32_t lds_max[8 * kWorkerMaxStride(NT / 64)];
-    __shared__ uint32_t lds_mmax[NT / 64];      // the mean's block maximum
-    // prefetched vectors, [stream (theta, replica 0..K-1)][run][wave][lane];
-    // every wave reads back only the 1 KB pieces it loaded itself
-    __shared__ f32x4 lds_pf[LP ? (K + 1) * G * NT : 1];
+    constexpr int V = 8, G = 2, W = V / G;       // two runs of 4 parameters a thread, 2,048 apart
+    constexpr int NS = 2 * K + 1;
+    constexpr int Q4 = (K + 3) / 4;              // groups of four workers
+    // workers whose next block streams into LDS (with theta up to 144 KB of the
+    // CU's 160); fp32 workers 9 and up come through registers
+    constexpr int LK = RT == RT_F32 && K > 8 ? 8 : K;
+    constexpr int RK = K - LK;
+    constexpr int RV = RT == RT_F32 ? G * NT : NT;   // 16-byte vectors of one replica's block
+    // theta stays in registers over the codes up to 8 workers; above, it is read
+    // from its LDS piece again for the update
+    constexpr bool KEEP_THETA = K <= 8;
+    // The momentum's loads go out while the codes are formed; with the reset and 4
+    // to 8 bf16 workers, before the next block's (100M, K = 8: 0.928 ms against
+    // 0.975, K = 4: 0.574 against 0.600; without the reset 0.603 against 0.575, and
+    // fp32 replicas run alike either way).
+    constexpr bool EARLY_V = RESET && RT == RT_BF16 && K >= 4 && K <= 8;
+    __shared__ uint32_t lds_max[(K <= 8 ? 8 : 16) * kWorkerMaxStride(NW)];
+    __shared__ uint32_t lds_mmax[NW];
+    // [theta: run][wave][lane], then [replica][run][wave][lane] (bf16: a wave's
+    // two 512-byte runs in one 1 KB piece); every wave reads back only the 1 KB
+    // pieces it loaded itself
+    __shared__ f32x4 lds_pf[G * NT + LK * RV];
 
-    // per-thread fp64 sums: in registers, or with the bf16 prefetch (which holds
-    // many registers) in this thread's own LDS slots, [sum][thread]
-    constexpr bool AL = PF;
-    double acc[AL ? 1 : NS];
-    __shared__ double lds_acc[AL ? NS * NT : 1];
-    auto acc_add = [&](int j, double x) {
-        if constexpr (AL)
-            lds_acc[j * NT + threadIdx.x] += x;
-        else
-            acc[j] += x;
-    };
+    double acc_s[STATS ? Q4 : 1], acc_q[STATS ? Q4 : 1], acc_m = 0.0;
 #pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        if constexpr (AL)
-            lds_acc[j * NT + threadIdx.x] = 0.0;
-        else
-            acc[j] = 0.0;
-    }
+    for (int j = 0; j < (STATS ? Q4 : 1); ++j) acc_s[j] = acc_q[j] = 0.0;
 
     const int64_t nfull = a.n / kCodecBlock;
     const int64_t nblocks = (a.n + kCodecBlock - 1) / kCodecBlock;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
 
-    // LDS prefetch: this wave's piece of stream s, run g
-    const int wave = threadIdx.x >> 6;
-    auto pf_piece = [&](int s, int g) { return lds_pf + ((s * G + g) * NW + wave) * 64; };
-    // Issues the (K + 1) * G direct loads of full block b: lane l's 16 bytes
-    // land at its wave's piece + 16 l.
-    auto pf_issue = [&](int64_t b) {
+    // Streams are addressed as a wave-uniform base (block and run) plus a 32-bit
+    // lane offset, and the LDS pieces as one lane index plus constants: neither
+    // leaves a per-lane pointer for each stream alive across the loop.
+    const uint32_t fo = threadIdx.x * 16u;        // byte offset of a thread's run in fp32 streams
+    auto fbase = [](const void* p, int64_t blk, int g) {
+        return static_cast<const char*>(p) + (blk * kCodecBlock + g * (kCodecBlock / 2)) * 4;
+    };
+    auto bbase = [](const void* p, int64_t blk, int g) {
+        return static_cast<const char*>(p) + (blk * kCodecBlock + g * (kCodecBlock / 2)) * 2;
+    };
+    // non-temporal (the last operand's bit 1), as every other access of the round: 5-30 % of the
+    // whole call on streams that no cache holds (8M, K = 8 fp32, no reset: 90 us
+    // against 130), and never slower than before where one does
+    auto to_lds = [&](const void* base, uint32_t off, int vec) {
+        __builtin_amdgcn_global_load_lds(
+            (const void __attribute__((address_space(1)))*)(static_cast<const char*>(base) + off),
+            (void __attribute__((address_space(3)))*)(lds_pf + vec + wave * 64), 16, 0, 2);
+    };
+    // Issues the direct loads of full block b: theta's, and the replicas'.
+    auto pf_theta = [&](int64_t b) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t o = b * kCodecBlock + g * (kCodecBlock / 2) + (int64_t)threadIdx.x * W;
+        for (int g = 0; g < G; ++g) to_lds(fbase(a.theta, b, g), fo, g * NT);
+    };
+    auto pf_replicas = [&](int64_t b) {
+        if constexpr (RT == RT_F32) {
+            uint32_t o = fo;
+            asm volatile("" : "+v"(o));   // no per-lane sums kept across the loop
 #pragma unroll
-            for (int s = 0; s <= K; ++s) {
-                const float* src = s == 0 ? a.theta + o : static_cast<const float*>(a.replicas[s - 1]) + o;
-                __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)src,
-                                                 (void __attribute__((address_space(3)))*)pf_piece(s, g), 16, 0, 0);
-            }
+            for (int k = 0; k < LK; ++k)
+#pragma unroll
+                for (int g = 0; g < G; ++g) to_lds(fbase(a.replicas[k], b, g), o, G * NT + k * RV + g * NT);
+        } else {
+            // lanes 0..31 the wave's first run (512 B), lanes 32..63 its second
+            uint32_t ro = (lane >> 5) * kCodecBlock + wave * 512u + (lane & 31) * 16u;
+            asm volatile("" : "+v"(ro));
+#pragma unroll
+            for (int k = 0; k < LK; ++k) to_lds(bbase(a.replicas[k], b, 0), ro, G * NT + k * RV);
         }
     };
-
-    // bf16: raw words (two per run), theta and (full blocks) momentum of one
-    // block (full: vector loads; else per element, zero beyond n)
-    // two register sets for the bf16 prefetch: the loop takes blocks in pairs and
-    // the sets swap roles (current / next) instead of being copied
-    u32x2 wA[KW][G], wB[PF ? KW : 1][G];
-    float tA[V], tB[PF ? V : 1];
-    float mA[PF ? V : 1], mB[PF ? V : 1];
-    auto load_bf16 = [&](int64_t b, auto& w, float (&t)[V], auto& m, auto full_c) {
-        constexpr bool FULL = decltype(full_c)::value;
+    f32x4 nx[RK > 0 ? RK : 1][G];   // the next block's vectors of workers LK..K-1
+    auto reg_issue = [&](int64_t b, int k) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t o = b * kCodecBlock + g * (kCodecBlock / 2) + (int64_t)threadIdx.x * W;
-            if constexpr (FULL) {
-                const f32x4 t4 = ld_f4(a.theta + o);
-#pragma unroll
-                for (int e = 0; e < W; ++e) t[g * W + e] = t4[e];
-                if constexpr (PF) {
-                    const f32x4 m4 = ld_f4(a.momentum + o);
-#pragma unroll
-                    for (int e = 0; e < W; ++e) m[g * W + e] = m4[e];
-                }
-#pragma unroll
-                for (int k = 0; k < KW; ++k)
-                    w[k][g] = __builtin_nontemporal_load(
-                        reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(a.replicas[k]) + o));
-            } else {
-                const int64_t left = a.n - o;
-#pragma unroll
-                for (int e = 0; e < W; ++e) t[g * W + e] = e < left ? a.theta[o + e] : 0.0f;
-#pragma unroll
-                for (int k = 0; k < KW; ++k) {
-                    const uint16_t* r = static_cast<const uint16_t*>(a.replicas[k]) + o;
-                    uint32_t h[W];
-#pragma unroll
-                    for (int e = 0; e < W; ++e) h[e] = e < left ? r[e] : 0u;
-                    w[k][g] = u32x2{h[0] | h[1] << 16, h[2] | h[3] << 16};
-                }
-            }
-        }
+        for (int g = 0; g < G; ++g) nx[k - LK][g] = ld_f4_at(fbase(a.replicas[k], b, g), fo);
     };
 
-    auto body = [&](int64_t blk, auto full_c, auto& cw, auto& cth, auto& cm, auto& nw, auto& nth, auto& nm) {
+    auto body = [&](int64_t blk, auto full_c) {
         constexpr bool FULL = decltype(full_c)::value;
+        const int64_t nb = blk + gridDim.x < nfull ? blk + gridDim.x : blk;
         int64_t off[G];
         int valid[G];
-        bool ok[V];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             off[g] = blk * kCodecBlock + g * (kCodecBlock / 2) + (int64_t)threadIdx.x * W;
-            if constexpr (FULL) {
-                valid[g] = W;
-            } else {
-                const int64_t left = a.n - off[g];
-                valid[g] = left >= W ? W : (left > 0 ? (int)left : 0);
-            }
-#pragma unroll
-            for (int e = 0; e < W; ++e) ok[g * W + e] = e < valid[g];
+            const int64_t left = a.n - off[g];
+            valid[g] = FULL || left >= W ? W : (left > 0 ? (int)left : 0);
         }
-
-        float th[V], v[V], d[RT == RT_F32 ? K : 1][V];
-        if constexpr (RT == RT_BF16) {
-            // momentum: from the prefetch, or loaded first (the update waits for
-            // it, and in-order completion then leaves the loads below in flight)
-            if constexpr (PF && FULL) {
-#pragma unroll
-                for (int e = 0; e < V; ++e) v[e] = cm[e];
-            } else
+        float th[V], v[V], d[K][V];
+        // momentum, first needed by the update
+        auto load_v = [&] {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int64_t o = off[g];
-                if constexpr (FULL) {
-                    const f32x4 v4 = ld_f4(a.momentum + o);
+                const f32x4 v4 = ld_f4_at(fbase(a.momentum, blk, g), fo);
 #pragma unroll
-                    for (int e = 0; e < W; ++e) v[g * W + e] = v4[e];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < W; ++e) v[g * W + e] = e < valid[g] ? a.momentum[o + e] : 0.0f;
-                }
+                for (int e = 0; e < W; ++e) v[g * W + e] = v4[e];
             }
-            if constexpr (PF && FULL) {
-                // next full block of this workgroup; on its last one, this block again
-                // (every iteration issues the same loads)
-                const int64_t nb = blk + gridDim.x < nfull ? blk + gridDim.x : blk;
-                load_bf16(nb, nw, nth, nm, BoolC<true>{});
-            } else {
-                load_bf16(blk, cw, cth, cm, full_c);
-            }
-#pragma unroll
-            for (int e = 0; e < V; ++e) th[e] = cth[e];
-        } else {
-            if constexpr (FULL && LP) {
-                // This block's direct loads were issued in the previous iteration
-                // (or before the loop), and every vector memory instruction issued
-                // after them is one of that iteration's stores: G of theta, G of
-                // v and, with the reset, G of each replica (more with the encoded
-                // mean).  In-order completion makes "at most that many
-                // outstanding" imply the loads have landed in LDS.
-                constexpr int after = G * (2 + (RESET ? K : 0));
-                __builtin_amdgcn_s_waitcnt((after & 0xF) | ((after >> 4) << 14) | 0x70 | 0xF00);
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int64_t o = off[g];
-                if constexpr (FULL && LP) {
-                    // theta and the replicas from the LDS prefetch (complete: see the
-                    // wait above), momentum from memory
-                    const int lane = threadIdx.x & 63;
-                    const f32x4 t4 = pf_piece(0, g)[lane], v4 = ld_f4(a.momentum + o);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        th[g * W + e] = t4[e];
-                        v[g * W + e] = v4[e];
-                    }
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const f32x4 r4 = pf_piece(k + 1, g)[lane];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) d[k][g * W + e] = th[g * W + e] - r4[e];
-                    }
-                } else if constexpr (FULL) {
-                    const f32x4 t4 = ld_f4(a.theta + o), v4 = ld_f4(a.momentum + o);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        th[g * W + e] = t4[e];
-                        v[g * W + e] = v4[e];
-                    }
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const f32x4 r4 = ld_f4(static_cast<const float*>(a.replicas[k]) + o);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) d[k][g * W + e] = th[g * W + e] - r4[e];
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < W; ++e) {
-                        const bool in = e < valid[g];
-                        const int x = g * W + e;
-                        th[x] = in ? a.theta[o + e] : 0.0f;
-                        v[x] = in ? a.momentum[o + e] : 0.0f;
-#pragma unroll
-                        for (int k = 0; k < K; ++k)
-                            d[k][x] = in ? th[x] - static_cast<const float*>(a.replicas[k])[o + e] : 0.0f;
-                    }
-                }
-            }
-        }
-        if constexpr (RT == RT_F32 && LP && FULL) {
-            // every LDS read of this block has returned before the next block's
-            // direct loads overwrite the pieces; then issue them (on the last
-            // block of this workgroup, this block again, so every iteration
-            // issues the same instructions; those values are not used)
-            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-            pf_issue(blk + gridDim.x < nfull ? blk + gridDim.x : blk);
-        }
-        // pseudo-gradient k of parameter e (bf16: from the raw replica word)
-        auto D = [&](int k, int e) -> float {
-            if constexpr (RT == RT_F32)
-                return d[k][e];
-            else
-                return th[e] - ((e & 1) ? bf16_hi(cw[k][e / W][(e % W) >> 1]) : bf16_lo(cw[k][e / W][(e % W) >> 1]));
         };
+        if constexpr (FULL) {
+            // This block's direct loads were issued in the previous iteration (or
+            // before the loop), and the last vector memory instructions issued
+            // after them are that iteration's stores: G of theta, G of v and, with
+            // the reset, G of each replica.  In-order completion makes "at most
+            // that many outstanding" imply the loads have landed in LDS.
+            constexpr int after = G * (2 + (RESET ? K : 0));
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(after) : "memory");
+            if constexpr (EARLY_V) load_v();
+            uint32_t li = threadIdx.x;
+            asm volatile("" : "+v"(li));
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const f32x4 t4 = lds_pf[g * NT + li];
+#pragma unroll
+                for (int e = 0; e < W; ++e) {
+                    th[g * W + e] = t4[e];
+                }
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    if constexpr (RT == RT_F32) {
+                        const f32x4 r4 = k < LK ? lds_pf[G * NT + k * RV + g * NT + li] : nx[k < LK ? 0 : k - LK][g];
+#pragma unroll
+                        for (int e = 0; e < W; ++e) d[k][g * W + e] = th[g * W + e] - r4[e];
+                    } else {
+                        const u32x2 w = reinterpret_cast<const u32x2*>(lds_pf + G * NT + k * RV)[g * 64 + (li >> 6) * 128 + (li & 63)];
+#pragma unroll
+                        for (int e = 0; e < W; ++e)
+                            d[k][g * W + e] = th[g * W + e] - ((e & 1) ? bf16_hi(w[e >> 1]) : bf16_lo(w[e >> 1]));
+                    }
+                }
+            }
+            // every LDS read of this block has returned before the next block's
+            // direct loads overwrite the pieces (on the workgroup's last block this
+            // block again, so that every iteration issues the same instructions;
+            // those values are not used)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if constexpr (KEEP_THETA) pf_theta(nb);
+            pf_replicas(nb);
+        } else {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int e = 0; e < W; ++e) {
+                    const bool in = e < valid[g];
+                    const int x = g * W + e;
+                    const int64_t o = off[g] + e;
+                    th[x] = in ? a.theta[o] : 0.0f;
+                    v[x] = in ? a.momentum[o] : 0.0f;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        float r = 0.0f;
+                        if (in) {
+                            if constexpr (RT == RT_F32)
+                                r = static_cast<const float*>(a.replicas[k])[o];
+                            else
+                                r = __uint_as_float((uint32_t) static_cast<const uint16_t*>(a.replicas[k])[o] << 16);
+                        }
+                        d[k][x] = th[x] - r;
+                    }
+                }
+        }
 
         // local-drift energy before quantisation
         if constexpr (STATS) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                float s = 0.f;
+            for (int j = 0; j < Q4; ++j) {
+                float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < V; ++e) s = __builtin_fmaf(D(k, e), D(k, e), s);
-                acc_add(k, (double)s);
+                for (int i = 0; i < 4; ++i)
+                    if (4 * j + i < K) {
+#pragma unroll
+                        for (int e = 0; e < V; ++e) s[i] = __builtin_fmaf(d[4 * j + i][e], d[4 * j + i][e], s[i]);
+                    }
+                quad_add(acc_s[j], s[0], s[1], s[2], s[3]);
             }
         }
 
-        // worker block scales
+        // worker block maxima: lane l gets worker (l mod 8)'s, or above 8 workers (l mod 16)'s
         float amax[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             float m = 0.f;
 #pragma unroll
-            for (int e = 0; e < V; ++e) m = fmaxf(m, fabsf(D(k, e)));
+            for (int e = 0; e < V; ++e) m = fmaxf(m, fabsf(d[k][e]));
             amax[k] = m;
         }
-        const float am = worker_block_max<K, NT / 64>(amax, lds_max);   // worker (lane mod 8)'s
-
-        // The K scales and their reciprocals are the same in every lane: lane k
-        // computes worker k's (one IEEE division of each kind for all workers
-        // instead of K), and every lane reads them back.
-        float scale_k[K], recip_k[K];
-        {
-            const float sv = codec_scale(am);
-            const float rv = 1.0f / sv;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                scale_k[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sv), k));
-                recip_k[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rv), k));
-            }
-        }
+        const float am = worker_block_max<K, NW>(amax, lds_max);
+        if constexpr (FULL && !EARLY_V) load_v();
+        // one division of each kind for all workers: lane k computes worker k's
+        const float sv = codec_scale(am);
+        const float rv = 1.0f / sv;
 
         // decode every worker and average: fp64 sum in worker order, times fp64(1/K)
         double sum[V];
@@ -494,43 +437,91 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
         for (int e = 0; e < V; ++e) sum[e] = 0.0;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const float s = scale_k[k];
-            const float r = recip_k[k];
+            const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sv), k));
+            const float r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rv), k));
             float q[V];
-            codec_q<V>([&](int e) { return D(k, e); }, s, r, q);
+            codec_q<V>([&](int e) { return d[k][e]; }, s, r, q);
 #pragma unroll
-            for (int e = 0; e < V; ++e) sum[e] += (double)(q[e] * s);
+            for (int e = 0; e < V; ++e) {
+                sum[e] += (double)(q[e] * s);
+                // the sum is taken here: left alone, the compiler moves every worker's
+                // additions past the codec's branches to one place at the end and keeps
+                // all K * 8 codes in registers until then
+                asm volatile("" : "+v"(sum[e]));
+            }
         }
         float mean[V];
-        float mmax[1] = {0.f};
+        float mmax = 0.f;
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             mean[e] = (float)(sum[e] * a.inv_k);
-            mmax[0] = fmaxf(mmax[0], fabsf(mean[e]));
+            mmax = fmaxf(mmax, fabsf(mean[e]));
         }
-        block_max<1, NT>(mmax, lds_mmax);
-        const float sm = codec_scale(mmax[0]);
+        block_max<NT>(mmax, lds_mmax);
+        const float sm = codec_scale(mmax);
         const float rm = 1.0f / sm;
 
         float agg[V], qm[V];
         codec_q<V>([&](int e) { return mean[e]; }, sm, rm, qm);
 #pragma unroll
-        for (int e = 0; e < V; ++e) agg[e] = ok[e] ? qm[e] * sm : 0.0f;
+        for (int e = 0; e < V; ++e) agg[e] = FULL || e % W < valid[e / W] ? qm[e] * sm : 0.0f;
+
+        if constexpr (FULL) {
+            // the momentum is waited for before any further load is issued
+#pragma unroll
+            for (int e = 0; e < V; ++e) asm volatile("" : "+v"(v[e]));
+        }
+        if constexpr (FULL && !KEEP_THETA) {
+            uint32_t li = threadIdx.x;
+            asm volatile("" : "+v"(li));
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const f32x4 t4 = lds_pf[g * NT + li];
+#pragma unroll
+                for (int e = 0; e < W; ++e) th[g * W + e] = t4[e];
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            pf_theta(nb);
+        }
+
+        // deviations from the aggregate; a worker's pseudo-gradients are not used
+        // after this, so its next block can be loaded into their registers
+#pragma unroll
+        for (int j = 0; j < Q4; ++j) {
+            if constexpr (STATS) {
+                float q[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (4 * j + i < K) {
+#pragma unroll
+                        for (int e = 0; e < V; ++e) {
+                            const float t = d[4 * j + i][e] - agg[e];
+                            q[i] = __builtin_fmaf(t, t, q[i]);
+                        }
+                    }
+                quad_add(acc_q[j], q[0], q[1], q[2], q[3]);
+            }
+            if constexpr (FULL && RK > 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (4 * j + i >= LK && 4 * j + i < K) reg_issue(nb, 4 * j + i);
+            }
+        }
+        if constexpr (STATS) {
+            float m = 0.f;
+#pragma unroll
+            for (int e = 0; e < V; ++e) m = __builtin_fmaf(agg[e], agg[e], m);
+            acc_m += (double)m;
+        }
+
         if (a.mean_codes != nullptr) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 if (FULL || valid[g] == W) {
-                    uint32_t w[W / 4];
+                    uint32_t w = 0;
 #pragma unroll
-                    for (int h = 0; h < W / 4; ++h) {
-                        w[h] = 0;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) w[h] |= (uint32_t)(uint8_t)(int8_t)qm[g * W + 4 * h + e] << (8 * e);
-                    }
-                    if constexpr (W == 4)
-                        __builtin_nontemporal_store(w[0], reinterpret_cast<uint32_t*>(a.mean_codes + off[g]));
-                    else
-                        __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2*>(a.mean_codes + off[g]));
+                    for (int e = 0; e < W; ++e) w |= (uint32_t)(uint8_t)(int8_t)qm[g * W + e] << (8 * e);
+                    __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(a.mean_codes + off[g]));
                 } else {
 #pragma unroll
                     for (int e = 0; e < W; ++e)
@@ -540,53 +531,32 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
             if (threadIdx.x == 0) a.mean_scales[blk] = sm;
         }
 
-        if constexpr (STATS) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                float q = 0.f;
-#pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    const float t = D(k, e) - agg[e];
-                    q = __builtin_fmaf(t, t, q);
-                }
-                acc_add(K + k, (double)q);
-            }
-            float m = 0.f;
-#pragma unroll
-            for (int e = 0; e < V; ++e) m = __builtin_fmaf(agg[e], agg[e], m);
-            acc_add(2 * K, (double)m);
-        }
-
         // corrected Nesterov step with the decoded aggregate, and the reset
-        float th_new[V], v_new[V];
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-            const float dt = agg[e] * a.scale;
-            v_new[e] = __builtin_fmaf(a.mu, v[e], dt);
-            const float dir = __builtin_fmaf(a.mu, v_new[e], dt);
-            th_new[e] = __builtin_fmaf(-a.eta, dir, th[e]);
-        }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int64_t o = off[g];
-            const float* tn = th_new + g * W;
-            const float* vn = v_new + g * W;
-            if (FULL || valid[g] == W) {
+            float tn[W], vn[W];
 #pragma unroll
-                for (int h = 0; h < W / 4; ++h) {
-                    st_f4(a.theta + o + 4 * h, f32x4{tn[4 * h], tn[4 * h + 1], tn[4 * h + 2], tn[4 * h + 3]});
-                    st_f4(a.momentum + o + 4 * h, f32x4{vn[4 * h], vn[4 * h + 1], vn[4 * h + 2], vn[4 * h + 3]});
-                }
+            for (int e = 0; e < W; ++e) {
+                const int x = g * W + e;
+                const float dt = agg[x] * a.scale;
+                vn[e] = __builtin_fmaf(a.mu, v[x], dt);
+                const float dir = __builtin_fmaf(a.mu, vn[e], dt);
+                tn[e] = __builtin_fmaf(-a.eta, dir, th[x]);
+            }
+            if (FULL || valid[g] == W) {
+                const f32x4 t4 = {tn[0], tn[1], tn[2], tn[3]};
+                st_f4_at(const_cast<char*>(fbase(a.theta, blk, g)), fo, t4);
+                st_f4_at(const_cast<char*>(fbase(a.momentum, blk, g)), fo, f32x4{vn[0], vn[1], vn[2], vn[3]});
                 if constexpr (RESET) {
                     if constexpr (RT == RT_F32) {
-                        const f32x4 t4 = {tn[0], tn[1], tn[2], tn[3]};
 #pragma unroll
-                        for (int k = 0; k < K; ++k) st_f4(static_cast<float*>(a.replicas[k]) + o, t4);
+                        for (int k = 0; k < K; ++k) st_f4_at(const_cast<char*>(fbase(a.replicas[k], blk, g)), fo, t4);
                     } else {
                         const u32x2 w = {bf16_pack(tn[0], tn[1]), bf16_pack(tn[2], tn[3])};
 #pragma unroll
                         for (int k = 0; k < K; ++k)
-                            __builtin_nontemporal_store(w, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(a.replicas[k]) + o));
+                            st_u2_at(const_cast<char*>(bbase(a.replicas[k], blk, g)), fo / 2, w);
                     }
                 }
             } else {
@@ -610,38 +580,31 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
         }
     };
 
-    if constexpr (PF) {
-        if (blockIdx.x < nfull) load_bf16(blockIdx.x, wA, tA, mA, BoolC<true>{});
-        // the first block's words are complete before the loop
-        __builtin_amdgcn_s_waitcnt(0);
-        // blocks in pairs: the first of a pair prefetches into B, the second into A
-        for (int64_t blk = blockIdx.x; blk < nfull; blk += 2 * (int64_t)gridDim.x) {
-            body(blk, BoolC<true>{}, wA, tA, mA, wB, tB, mB);
-            if (blk + gridDim.x >= nfull) break;
-            body(blk + gridDim.x, BoolC<true>{}, wB, tB, mB, wA, tA, mA);
-        }
-    } else {
-        if constexpr (LP) {
-            if (blockIdx.x < nfull) pf_issue(blockIdx.x);
-            __builtin_amdgcn_s_waitcnt(0);   // the first block's pieces are in LDS
-        }
-        for (int64_t blk = blockIdx.x; blk < nfull; blk += gridDim.x) body(blk, BoolC<true>{}, wA, tA, mA, wB, tB, mB);
-        // the last iteration's direct loads (a re-read, unused) land before anything
-        // else uses this workgroup's LDS or the workgroup ends
-        if constexpr (LP) __builtin_amdgcn_s_waitcnt(0);
+    if (blockIdx.x < nfull) {
+        pf_theta(blockIdx.x);
+        pf_replicas(blockIdx.x);
+#pragma unroll
+        for (int k = LK; k < K; ++k) reg_issue(blockIdx.x, k);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the first block's pieces are in LDS
+    for (int64_t blk = blockIdx.x; blk < nfull; blk += gridDim.x) body(blk, BoolC<true>{});
+    // the last iteration's direct loads (a re-read, unused) land before anything
+    // else uses this workgroup's LDS or the workgroup ends
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // the shorter last block belongs to the workgroup the grid stride gives it
-    if (nfull < nblocks && nfull % gridDim.x == blockIdx.x) body(nfull, BoolC<false>{}, wA, tA, mA, wB, tB, mB);
+    if (nfull < nblocks && nfull % gridDim.x == blockIdx.x) body(nfull, BoolC<false>{});
 
     if constexpr (STATS) {
-        if constexpr (AL) {
-            double r[NS];
+        // back to one value per sum and lane (a sum's other lanes hold zeros)
+        const int mine = threadIdx.x & 3;
+        double r[NS];
 #pragma unroll
-            for (int j = 0; j < NS; ++j) r[j] = lds_acc[j * NT + threadIdx.x];
-            store_partials<NS, NT>(r, a.partials);
-        } else {
-            store_partials<NS, NT>(acc, a.partials);
+        for (int k = 0; k < K; ++k) {
+            r[k] = mine == k % 4 ? acc_s[k / 4] : 0.0;
+            r[K + k] = mine == k % 4 ? acc_q[k / 4] : 0.0;
         }
+        r[2 * K] = acc_m;
+        store_partials<NS, NT>(r, a.partials);
     }
 }
 
@@ -655,7 +618,5 @@ hipError_t launch_int8_bf16_s0r0(int, int, hipStream_t, const Int8Args&);
 hipError_t launch_int8_bf16_s0r1(int, int, hipStream_t, const Int8Args&);
 hipError_t launch_int8_bf16_s1r0(int, int, hipStream_t, const Int8Args&);
 hipError_t launch_int8_bf16_s1r1(int, int, hipStream_t, const Int8Args&);
-int occupancy_int8_f32_s1r1(int k);
-int occupancy_int8_bf16_s1r1(int k);
 
 }  // namespace autoloco

@@ -210,14 +210,12 @@ def test_codes_at_rounding_boundaries(ctx, dtype, k):
 
 
 @pytest.mark.parametrize("grid", [1, 2, 3])
-@pytest.mark.parametrize("dtype,k", [(torch.bfloat16, 8), (torch.bfloat16, 9), (torch.bfloat16, 16),
-                                     (torch.float32, 8), (torch.float32, 9), (torch.float32, 13), (torch.float32, 16)])
+@pytest.mark.parametrize("dtype,k", [(torch.bfloat16, 8), (torch.bfloat16, 16), (torch.float32, 8)])
 def test_many_blocks_per_workgroup(ctx, grid, dtype, k):
     # a capped grid gives every workgroup several codec blocks, even and odd
     # counts, so the prefetching loops go round (bf16 up to K = 8: blocks in pairs
     # with the two register sets swapping roles; fp32 up to K = 8: the LDS
-    # prefetch; above 8 workers both replica types: the LDS prefetch, with workers 9
-    # and up of fp32 through registers) and the ragged last block follows them
+    # prefetch) and the ragged last block follows them
     al.autoloco_set_grid_limit(ctx, grid)
     try:
         _check(ctx, 7 * 4096 + 100, k, dtype=dtype, seed=50 + grid + k, normalize=grid % 2 == 1)
@@ -256,27 +254,3 @@ def test_non_finite_blocks_stay_local(ctx, k, dtype):
         assert got_scales[b].view(np.uint32) == ref.mean_scales[b].view(np.uint32), b
         assert_close_elementwise(th[lo:hi], ref.theta[lo:hi], what=f"theta' block {b}")
         assert_close_elementwise(v[lo:hi], ref.momentum[lo:hi], what=f"v' block {b}")
-
-
-@pytest.mark.parametrize("k,dtype", [(9, torch.float32), (12, torch.bfloat16), (16, torch.float32), (16, torch.bfloat16)])
-@pytest.mark.parametrize("flags", [0, al.FUSE_STATS, al.FUSE_RESET])
-def test_wide_variants_agree(ctx, k, dtype, flags):
-    # 9 to 16 workers: every flag subset takes the same step, bit for bit, as the
-    # call with both flags (which the tests above compare with the oracle), over
-    # several blocks per workgroup and a ragged last one
-    n = 9 * 4096 + 1001
-    inp = cpu_inputs(n, k, seed=90 + k, replica_dtype=dtype)
-    c = al.make_coeffs(COEFFS["mu"], COEFFS["eta_out"], COEFFS["rho"], True)
-    al.autoloco_set_grid_limit(ctx, 2)
-    try:
-        a, b = to_device(inp), to_device(inp)
-        want = al.autoloco_outer_step_int8(ctx, a.theta, a.momentum, a.replicas, c, al.FUSE_STATS | al.FUSE_RESET, EPS)
-        got = al.autoloco_outer_step_int8(ctx, b.theta, b.momentum, b.replicas, c, flags, EPS)
-        torch.cuda.synchronize()
-    finally:
-        al.autoloco_set_grid_limit(ctx, 0)
-    assert torch.equal(a.theta, b.theta) and torch.equal(a.momentum, b.momentum)
-    for x, y, z in zip(a.replicas, b.replicas, inp.replicas):
-        assert torch.equal(y, x if flags & al.FUSE_RESET else z.cuda())
-    if flags & al.FUSE_STATS:
-        assert bytes(got) == bytes(want)
