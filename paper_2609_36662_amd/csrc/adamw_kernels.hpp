@@ -31,7 +31,7 @@ namespace autoloco {
 struct GradNormArgs {
     const float* grads[kMaxK];
     int64_t n;
-    double* partials;      // [gridDim.x][K] per-workgroup squared norms
+    double* partials;      // [K][gridDim.x] per-workgroup squared norms
 };
 
 struct AdamWArgs {

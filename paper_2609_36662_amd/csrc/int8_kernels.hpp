@@ -38,7 +38,7 @@ struct Int8Args {
     double inv_k;
     int8_t* mean_codes;   // [n] or null
     float* mean_scales;   // [ceil(n / 4096)] or null
-    double* partials;     // [gridDim.x][2K+1] per-workgroup sums
+    double* partials;     // [2K+1][gridDim.x] per-workgroup sums
 };
 
 __device__ __forceinline__ float codec_scale(float amax) {

@@ -17,7 +17,7 @@
 // displace one another in the caches, in a grid-stride loop over a fixed
 // grid.  Elementwise arithmetic is fp32; the squared sums of one vector are
 // added in fp32 and then into per-lane fp64 running sums.  The 2K+1 sums are
-// reduced deterministically: a wavefront butterfly, then the waves of the
+// reduced deterministically: halving exchanges in a wavefront, then the waves of the
 // workgroup in order through LDS into one partial per workgroup (a plain
 // store), then a one-workgroup kernel launched after this one on the same
 // stream adds the partials in workgroup order.  With the grid fixed, every
@@ -51,7 +51,7 @@ struct RoundArgs {
     void* replicas[kMaxK];
     int64_t n;
     float mu, eta, scale, inv_k;
-    double* partials;      // [gridDim.x][2K+1] per-workgroup sums
+    double* partials;      // [2K+1][gridDim.x] per-workgroup sums
     uint16_t* payload;     // BF16 payload modes: [n] bits of the received mean, or null
     double inv_k64;        // 1/K in float64 (BF16 payload modes)
 };
