@@ -141,13 +141,31 @@ int blocks_for(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k, bool bf
     return static_cast<int>(want < limit ? want : limit);
 }
 
-// Workgroups per worker of the AdamW update: about two per compute unit in
-// total, split evenly over the workers' grid rows (measured at 1.1B, K = 8 on
-// MI355X: 512 workgroups 2-3 % faster than 768, 1,024 or 2,048).
+// Grid of the standalone reset: as blocks_for without the round's rule, except the
+// copy into one fp32 replica in spans of four windows (reset_span4), one workgroup
+// per compute unit, and one or two bf16 replicas from 100M parameters on, two
+// (MI355X: 1.1B K = 1 1.10 ms at 512 against 1.20 at 768, K = 2 1.57-1.66 against
+// 1.65; 400M K = 1 388 us against 406; 30M 32.7 against 31.7).
+int reset_blocks(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k) {
+    const int blocks = blocks_for(ctx, n, dtype, k, false, false);
+    if (ctx->grid_limit > 0) return blocks;
+    const bool bf16 = dtype == AUTOLOCO_BF16;
+    const int most = !bf16 && k == 1 && reset_span4(n)            ? ctx->num_cus
+                     : bf16 && k <= 2 && n >= 100 * 1000 * 1000 ? ctx->num_cus * 2
+                                                                  : blocks;
+    return blocks < most ? blocks : most;
+}
+
+// Workgroups per worker of the AdamW update: one per compute unit in total from
+// 16M worker-parameters on, two below, split evenly over the workers' grid rows and
+// never beyond (one workgroup more than the units hold at once runs alone at the
+// end).  MI355X, plain allocations, update pass: 124M K = 4 2.50 ms at 256 against
+// 2.60 at 512, K = 8 5.11 against 5.38, K = 1 0.59 against 0.63; 5M K = 4 99 us
+// against 103, but K = 1 29.0 against 28.4; 1M alike.
 int adamw_blocks(const autoloco_ctx* ctx, int64_t n, int k) {
-    int limit = ctx->grid_limit > 0 ? ctx->grid_limit : ctx->num_cus * 2;
+    int limit = ctx->grid_limit > 0 ? ctx->grid_limit : ctx->num_cus * (n >= (int64_t(16) << 20) / k ? 1 : 2);
     if (limit > kMaxBlocks) limit = kMaxBlocks;
-    int per = (limit + k - 1) / k;
+    int per = limit / k;
     const int64_t want = (n / 4 + kBlock - 1) / kBlock;
     if (want < per) per = static_cast<int>(want);
     return per < 1 ? 1 : per;
@@ -398,11 +416,8 @@ int run_one_sum(autoloco_ctx* c, Launch launch, int blocks, double* out) {
 }
 
 // Workgroups of the per-GPU share kernels (two quads of 4 parameters per lane
-// per window): the payload kernel two per CU, the shard step three (measured on
-// MI355X with both kernels loading both runs before any store: payload 1.1B
-// 1.93 ms at 512 against 1.98 at 768; shard step 3B K = 8 2.27 ms at 768 against
-// 2.40 at 512, 2.31 at 1,024, and equal at 1.1B).
-int blocks8(const autoloco_ctx* ctx, int64_t n, int per_cu = 2) {
+// per window), at per_cu a compute unit.
+int blocks8(const autoloco_ctx* ctx, int64_t n, int per_cu) {
     int limit = ctx->grid_limit > 0 ? ctx->grid_limit : ctx->num_cus * per_cu;
     if (limit > kMaxBlocks) limit = kMaxBlocks;
     int64_t want = (n / 8 + kBlock - 1) / kBlock;
@@ -772,7 +787,7 @@ int autoloco_broadcast_reset(autoloco_ctx* c, const autoloco_buffers* b) {
     DeviceGuard g(c->device);
     if (!g.ok) return fail(c, AUTOLOCO_E_DEVICE, "hipSetDevice failed");
     RoundArgs a = make_args(c, b);
-    const int blocks = blocks_for(c, b->n, b->replica_dtype, b->k, false, false);
+    const int blocks = reset_blocks(c, b->n, b->replica_dtype, b->k);
     int ts = timer_start(c);
     if (ts != AUTOLOCO_OK) return ts;
     hipError_t e = launch_reset(b->replica_dtype == AUTOLOCO_BF16 ? RT_BF16 : RT_F32, b->k, blocks, c->stream, a);
@@ -979,8 +994,12 @@ int autoloco_rank_payload(autoloco_ctx* c, int64_t n, const float* theta, const 
     a.payload = payload;
     a.n = n;
     a.partials = c->partials;
-    const int blocks = blocks8(c, n);
+    // Two workgroups a CU, or one for fp32 replicas from 256M parameters on, where
+    // two 8 KB reads and a 4 KB write a workgroup fill the memory (MI355X: 1.1B fp32
+    // 1.86-1.90 ms at 256 against 1.98-2.01 at 512, 400M 671 us against 711; 124M 212
+    // against 208, 30M 56 against 53; bf16 1.1B 1.72 ms against 1.53).
     const int rt = dtype == AUTOLOCO_BF16 ? RT_BF16 : RT_F32;
+    const int blocks = blocks8(c, n, rt == RT_F32 && n >= (int64_t(1) << 28) ? 1 : 2);
     return run_one_sum(c, [&] { return launch_rank_payload(rt, blocks, c->stream, a); }, blocks, sq_norm);
 }
 
@@ -1022,7 +1041,10 @@ int autoloco_shard_step(autoloco_ctx* c, const autoloco_shard_buffers* b, const 
     a.scale = co->normalize ? static_cast<float>(1.0 / co->rho) : 1.0f;
     a.inv_k64 = 1.0 / static_cast<double>(b->k);
     a.partials = c->partials;
-    const int blocks = blocks8(c, b->n, 3);
+    // One workgroup a CU from 4M parameters on, three below (MI355X, 1.1B / 8 K = 8
+    // 720-795 us at 256 against 833 at 768, 275M K = 1 0.82 ms against 0.95, 25M K = 16
+    // 206 us against 216; 7.5M alike; 1.9M K = 16 24.2 us against 22.9).
+    const int blocks = blocks8(c, b->n, b->n >= (int64_t(4) << 20) ? 1 : 3);
     const int k = b->k;
     return run_one_sum(c, [&] { return launch_shard_step(k, blocks, c->stream, a); }, blocks, sq_mean);
 }
@@ -1148,8 +1170,9 @@ namespace {
 // Windows of 256 quads per workgroup and iteration.  fp32 replicas: 8 from
 // three replicas on, where the longer contiguous writes per replica are 3-10 %
 // faster than one window on MI355X (1.1B: K = 8 6.20-6.28 ms against 6.64-6.85,
-// K = 6 4.83-4.88 against 5.37-5.53), one below (a copy at K = 1, which runs no
-// faster with longer spans).  bf16 replicas: two windows (a 4 KB run per
+// K = 6 4.83-4.88 against 5.37-5.53), one below, but four for the copy at K = 1 from
+// 4M parameters on, at one workgroup per CU (1.1B 1.51-1.63 ms against 1.58-1.71,
+// 400M 561 us against 580, 30M 42 against 43).  bf16 replicas: two windows (a 4 KB run per
 // replica), faster than 4 to 16 at every K (3B, K = 8: 10.5 ms against 10.6-11.1;
 // K = 3: 5.1 against 5.5-6.1).
 template <int K>
@@ -1158,6 +1181,8 @@ hipError_t reset_k(int rt, int blocks, hipStream_t s, const RoundArgs& a) {
         hipLaunchKernelGGL((reset_kernel<K, RT_BF16, 2>), dim3(blocks), dim3(kBlock), 0, s, a);
     else if constexpr (K >= 3)
         hipLaunchKernelGGL((reset_kernel<K, RT_F32, 8>), dim3(blocks), dim3(kBlock), 0, s, a);
+    else if (K == 1 && reset_span4(a.n))
+        hipLaunchKernelGGL((reset_kernel<K, RT_F32, 4>), dim3(blocks), dim3(kBlock), 0, s, a);
     else
         hipLaunchKernelGGL((reset_kernel<K, RT_F32, 1>), dim3(blocks), dim3(kBlock), 0, s, a);
     return hipGetLastError();

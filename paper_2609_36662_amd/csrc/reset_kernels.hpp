@@ -66,6 +66,9 @@ __global__ void __launch_bounds__(kBlock) reset_kernel(RoundArgs a) {
     }
 }
 
+// The copy into one fp32 replica takes spans of four windows from this size on.
+inline bool reset_span4(int64_t n) { return n >= (int64_t(4) << 20); }
+
 hipError_t launch_reset(int rt, int k, int blocks, hipStream_t stream, const RoundArgs& a);
 
 }  // namespace autoloco
