@@ -16,8 +16,9 @@
 //                       m      = beta1 m + (1 - beta1) g
 //                       v      = beta2 v + (1 - beta2) g^2
 //                       theta -= (lr / (1 - beta1^t)) m / (sqrt(v) / sqrt(1 - beta2^t) + eps)
-// The clipping coefficient is computed in fp64 by every workgroup from the
-// sums pass 1 left in device memory, so the step needs no host round trip.
+// The clipping coefficient is computed in fp64 by every workgroup of pass 2 from
+// the per-workgroup sums pass 1 left in device memory, so the step needs neither a
+// host round trip nor a kernel between the passes.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,8 +42,11 @@ struct AdamWArgs {
     const float* grads[kMaxK];
     uint16_t* copy[kMaxK];   // BF16 copies of the new parameters, or all null
     int64_t n;
-    const double* norm_sq;   // [K] squared gradient norms, or null (no clipping)
-    double max_norm;
+    const double* partials;  // [K][nblocks] per-workgroup squared norms, or null (no norms)
+    int nblocks;
+    double max_norm;         // 0: no clipping
+    double* sums;            // [K] squared norms, written by each worker's first workgroup
+    double* host_sums;       // the same in coherent host memory, or null
     float decay;             // 1 - lr * weight_decay
     float beta1, beta2;
     float omb1, omb2;        // 1 - beta1, 1 - beta2
@@ -52,23 +56,47 @@ struct AdamWArgs {
     uint32_t mask;           // traffic reference only: 0 (a value the compiler cannot see)
 };
 
+// Windows of its grid-stride sequence a thread loads before it adds any of them
+// up (in that order, so every per-thread sum is what one window at a time gives):
+// one worker's stream alone keeps too few bytes in flight at three workgroups a CU.
+// (124M: K = 1 77 us against 109; from K = 3 on nothing is gained.)
+template <int K>
+constexpr int norm_unroll() {
+    return K == 1 ? 4 : K == 2 ? 2 : 1;
+}
+
 template <int K>
 __global__ void __launch_bounds__(kBlock) grad_norm_kernel(GradNormArgs a) {
+    constexpr int U = norm_unroll<K>();
     double acc[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) acc[k] = 0.0;
     const int64_t nvec = a.n / 4;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < nvec; i += stride) {
+    auto add = [&](int k, f32x4 g) {
+        float s = g[0] * g[0];
+        s = __builtin_fmaf(g[1], g[1], s);
+        s = __builtin_fmaf(g[2], g[2], s);
+        s = __builtin_fmaf(g[3], g[3], s);
+        acc[k] += (double)s;
+    };
+    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if constexpr (U > 1) {
+        for (; i + (U - 1) * stride < nvec; i += U * stride) {
+            f32x4 g[U][K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const f32x4 g = ld_f4(a.grads[k] + 4 * i);
-            float s = g[0] * g[0];
-            s = __builtin_fmaf(g[1], g[1], s);
-            s = __builtin_fmaf(g[2], g[2], s);
-            s = __builtin_fmaf(g[3], g[3], s);
-            acc[k] += (double)s;
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < K; ++k) g[u][k] = ld_f4(a.grads[k] + 4 * (i + u * stride));
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < K; ++k) add(k, g[u][k]);
         }
+    }
+    for (; i < nvec; i += stride) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) add(k, ld_f4(a.grads[k] + 4 * i));
     }
     if (blockIdx.x == 0 && threadIdx.x < (a.n & 3)) {
         const int64_t j = nvec * 4 + threadIdx.x;
@@ -113,7 +141,25 @@ __device__ __forceinline__ void adamw_keep(const AdamWArgs& a, float& p, float& 
 template <bool COPY, bool TRAFFIC>
 __global__ void __launch_bounds__(kBlock) adamw_kernel(AdamWArgs a) {
     const int k = blockIdx.y;
-    const float coef = !TRAFFIC && a.norm_sq != nullptr ? clip_coef(a.norm_sq[k], a.max_norm) : 1.0f;
+    float coef = 1.0f;
+    if (!TRAFFIC && a.partials != nullptr) {
+        // worker k's squared norm, added up in the order of the reductions' second
+        // stage by every workgroup (a few KB from the caches), instead of in a
+        // kernel between the passes
+        __shared__ double total;
+        double t[1] = {0.0};
+        for (int b = threadIdx.x; b < a.nblocks; b += kBlock) t[0] += a.partials[(int64_t)k * a.nblocks + b];
+        const double sum = block_reduce<1, kBlock>(t);
+        if (threadIdx.x == 0) {
+            total = sum;
+            if (blockIdx.x == 0) {
+                a.sums[k] = sum;
+                if (a.host_sums != nullptr) a.host_sums[k] = sum;
+            }
+        }
+        __syncthreads();
+        if (a.max_norm > 0.0) coef = clip_coef(total, a.max_norm);
+    }
     float* __restrict__ p = a.params[k];
     float* __restrict__ m = a.exp_avg[k];
     float* __restrict__ v = a.exp_avg_sq[k];
@@ -121,7 +167,7 @@ __global__ void __launch_bounds__(kBlock) adamw_kernel(AdamWArgs a) {
     uint16_t* __restrict__ c = a.copy[k];
     const int64_t nvec = a.n / 4;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < nvec; i += stride) {
+    auto quad = [&](int64_t i) {
         f32x4 pv = ld_f4(p + 4 * i), mv = ld_f4(m + 4 * i), vv = ld_f4(v + 4 * i);
         const f32x4 gv = ld_f4(g + 4 * i);
         float pe[4], me[4], ve[4];
@@ -141,7 +187,17 @@ __global__ void __launch_bounds__(kBlock) adamw_kernel(AdamWArgs a) {
         if constexpr (COPY)
             __builtin_nontemporal_store(u32x2v{bf16_pack(pe[0], pe[1]), bf16_pack(pe[2], pe[3])},
                                         reinterpret_cast<u32x2v*>(c + 4 * i));
+    };
+    // From the last window down: the norm pass read the gradients up to their ends
+    // just before, and what the Infinity Cache still holds of them comes first.
+    // (124M, K = 4: 2.57 ms against 2.60.)
+    const int64_t nw = (nvec + kBlock - 1) / kBlock;
+    int64_t i = (nw - 1 - blockIdx.x) * kBlock + threadIdx.x;
+    if (blockIdx.x == 0) {   // the last window may be short, or missing (n < 4)
+        if (i >= 0 && i < nvec) quad(i);
+        i -= stride;
     }
+    for (; i >= 0; i -= stride) quad(i);
     if (blockIdx.x == 0 && threadIdx.x < (a.n & 3)) {
         const int64_t j = nvec * 4 + threadIdx.x;
         float pe = p[j], me = m[j], ve = v[j];

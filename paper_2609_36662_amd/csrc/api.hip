@@ -1073,6 +1073,7 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
     DeviceGuard g(c->device);
     if (!g.ok) return fail(c, AUTOLOCO_E_DEVICE, "hipSetDevice failed");
     const bool norm_pass = clip || out != nullptr;
+    int nblocks = 0;
     int ts = timer_start(c);
     if (ts != AUTOLOCO_OK) return ts;
     hipError_t e;
@@ -1082,11 +1083,9 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
         for (int k = 0; k < b->k; ++k) na.grads[k] = b->grads[k];
         na.n = b->n;
         na.partials = c->partials;
-        const int nblocks = blocks_for(c, b->n, AUTOLOCO_F32, b->k, false, false);
+        nblocks = blocks_for(c, b->n, AUTOLOCO_F32, b->k, false, false);
         e = launch_grad_norm(b->k, nblocks, c->stream, na);
         if (e != hipSuccess) return hip_fail(c, e, "gradient norm launch");
-        e = launch_finish_sums(b->k, kBlock, nblocks, c->partials, c->sums, c->stream, c->host_sums_dev);
-        if (e != hipSuccess) return hip_fail(c, e, "reduction launch");
     }
     if (c->timing && (e = hipEventRecord(c->ev_mid, c->stream)) != hipSuccess) return hip_fail(c, e, "hipEventRecord");
     AdamWArgs a;
@@ -1099,8 +1098,11 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
         a.copy[k] = static_cast<uint16_t*>(b->model_bf16[k]);
     }
     a.n = b->n;
-    a.norm_sq = clip ? c->sums : nullptr;
+    a.partials = norm_pass ? c->partials : nullptr;
+    a.nblocks = nblocks;
     a.max_norm = co->max_grad_norm;
+    a.sums = c->sums;
+    a.host_sums = c->host_sums_dev;
     a.decay = static_cast<float>(1.0 - co->lr * co->weight_decay);
     a.beta1 = static_cast<float>(co->beta1);
     a.beta2 = static_cast<float>(co->beta2);
