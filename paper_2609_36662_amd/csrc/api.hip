@@ -107,32 +107,37 @@ int check_device_ptr(autoloco_ctx* ctx, uintptr_t p, const char* name) {
     return AUTOLOCO_OK;
 }
 
-// Default grid: from K = 5 with fp32 replicas and from K = 6 with bf16 one
-// workgroup per compute unit (4 waves), below that three, or fewer if fewer fit
-// (the fused kernel's occupancy).  Measured on MI355X (256 CUs) with the
-// round's buffers spread in HBM, 1.1B K = 8 fp32: fused round 14.14-14.27 ms at
-// 256 workgroups against 14.37-14.57 at 768 (the traffic reference alike), and
-// no mode slower (statistics only 6.28 against 6.37 ms, with its windows loaded
-// ahead); 3B K = 8 bf16, GPT-2 small K = 8 and K = 12-16 gain 1-3 % too, fp32
-// K = 5-7 every mode 0-5 %, bf16 K = 6-7 the fused round by 2 % (3B).  At K = 4
-// the fused round gains 1 % but the statistics-only mode and the update with
-// statistics lose 3-9 % (the update without them and the reset alone 10-23 %),
-// and below K = 4 the statistics-only mode needs more waves, so those keep 768.
-// Even multiples of 256 are the slowest.  Every mode of a given (k, replica type) uses the same
-// grid, so the statistics of a standalone and of a fused call are summed in the
-// same order, bit for bit.
-// round_grid = false: a kernel with no statistics to keep in step with the
-// round's modes (the reset alone, AdamW's gradient-norm pass), which keeps three
-// per compute unit at every K.
-int blocks_for(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k, bool bf16p = false,
-               bool round_grid = true) {
+// Workgroups per compute unit of the round's modes.  One with statistics, so that
+// every mode of a given (k, replica type) adds them up in the same order, bit for
+// bit, and from K = 5 with fp32 replicas or K = 6 with bf16 (1.1B K = 8 fp32, buffers
+// spread in HBM: fused round 14.14-14.27 ms at 256 workgroups against 14.37-14.57 at
+// 768; 3B K = 8 bf16, GPT-2 small K = 8 and K = 12-16 gain 1-3 % too).  With fewer
+// replicas, on plain allocations:
+//   fused, 124M: fp32 K = 4 1.09-1.16 ms against 1.18-1.22 at 768, K = 2 0.70 against
+//     0.80, K = 1 0.52-0.53 against 0.55-0.58; bf16 K = 4 0.71 against 0.78, K = 1 0.42
+//     against 0.48; 10M fp32 K = 4 93 us against 104;
+//   statistics alone and the update with them no slower, with their windows ahead
+//     (124M fp32 K = 4 0.37 and 0.72 ms either way; bf16 0.22 against 0.24 and 0.51
+//     against 0.55).
+// Without statistics: one for bf16 replicas from 16M parameters on (30M K = 4 +5 %; 4M
+// K = 4 26.8 us against 25.6) and for the reset of fp32 ones from 8M replica
+// parameters on (4M K = 4 43 us against 49; 1M K = 1 9.0 against 8.5), three for the
+// plain update of fp32 replicas (124M K = 2 0.53 ms against 0.68 at 256).
+// Even multiples of 256 are the slowest.
+int round_per_cu(int64_t n, int32_t dtype, int k, bool stats, bool reset) {
+    const bool bf16 = dtype == AUTOLOCO_BF16;
+    if (stats || k >= (bf16 ? 6 : 5)) return 1;
+    if (bf16) return n >= (int64_t(16) << 20) ? 1 : 3;
+    return reset && n >= (int64_t(8) << 20) / k ? 1 : 3;
+}
+
+// Workgroups of a kernel that takes four fp32 or eight bf16 parameters a lane, per_cu
+// a compute unit or fewer if the fused kernel's registers fit fewer.
+int blocks_for(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k, int per_cu, bool bf16p = false) {
     const int64_t v = dtype == AUTOLOCO_BF16 ? 8 : 4;
     const int64_t nvec = n / v;
-    int per_cu = (bf16p ? ctx->occupancy_bf16p : ctx->occupancy)[dtype == AUTOLOCO_BF16 ? 1 : 0][k];
-    if (per_cu > 3) per_cu = 3;
-    // one workgroup per CU for the round's modes from K = 5 (fp32) or 6 (bf16
-    // replicas), where the modes are as fast or faster than at three
-    if (round_grid && k >= (dtype == AUTOLOCO_BF16 ? 6 : 5)) per_cu = 1;
+    const int fit = (bf16p ? ctx->occupancy_bf16p : ctx->occupancy)[dtype == AUTOLOCO_BF16 ? 1 : 0][k];
+    if (per_cu > fit) per_cu = fit;
     if (per_cu < 1) per_cu = 1;
     int limit = ctx->grid_limit > 0 ? ctx->grid_limit : ctx->num_cus * per_cu;
     if (limit > kMaxBlocks) limit = kMaxBlocks;
@@ -141,13 +146,18 @@ int blocks_for(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k, bool bf
     return static_cast<int>(want < limit ? want : limit);
 }
 
-// Grid of the standalone reset: as blocks_for without the round's rule, except the
+// Grid of the fused round (update, statistics and reset).
+int fused_blocks(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k) {
+    return blocks_for(ctx, n, dtype, k, round_per_cu(n, dtype, k, true, true));
+}
+
+// Grid of the standalone reset: three workgroups per compute unit, except the
 // copy into one fp32 replica in spans of four windows (reset_span4), one workgroup
 // per compute unit, and one or two bf16 replicas from 100M parameters on, two
 // (MI355X: 1.1B K = 1 1.10 ms at 512 against 1.20 at 768, K = 2 1.57-1.66 against
 // 1.65; 400M K = 1 388 us against 406; 30M 32.7 against 31.7).
 int reset_blocks(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k) {
-    const int blocks = blocks_for(ctx, n, dtype, k, false, false);
+    const int blocks = blocks_for(ctx, n, dtype, k, 3);
     if (ctx->grid_limit > 0) return blocks;
     const bool bf16 = dtype == AUTOLOCO_BF16;
     const int most = !bf16 && k == 1 && reset_span4(n)            ? ctx->num_cus
@@ -305,7 +315,10 @@ int sums_to_host(autoloco_ctx* c, size_t count) {
 // sums and fills *out.
 int run_round(autoloco_ctx* ctx, const autoloco_buffers* b, const RoundArgs& a, int mode, bool stats,
               double eps, autoloco_stats* out) {
-    const int blocks = blocks_for(ctx, b->n, b->replica_dtype, b->k, mode >= MODE_P_UPDATE);
+    const int plain = mode >= MODE_P_UPDATE ? mode - 4 : mode;   // the mode with the same outputs
+    const bool reset = plain == MODE_UPDATE_RESET || plain == MODE_UPDATE_STATS_RESET;
+    const int blocks = blocks_for(ctx, b->n, b->replica_dtype, b->k,
+                                  round_per_cu(b->n, b->replica_dtype, b->k, stats, reset), mode >= MODE_P_UPDATE);
     int ts = timer_start(ctx);
     if (ts != AUTOLOCO_OK) return ts;
     hipError_t e = launcher(b->replica_dtype, mode)(b->k, blocks, ctx->stream, a);
@@ -532,7 +545,7 @@ int autoloco_outer_step_static(int device, void* stream, const autoloco_buffers*
         if (stats) zero_stats(b->k, eps, out);
         return AUTOLOCO_OK;
     }
-    if (blocks_for(&c, b->n, b->replica_dtype, b->k) > kStaticBlocks) return AUTOLOCO_E_INVALID;
+    if (fused_blocks(&c, b->n, b->replica_dtype, b->k) > kStaticBlocks) return AUTOLOCO_E_INVALID;
     RoundArgs a = make_args(&c, b);
     set_step(a, co);
     const int mode = stats ? (reset ? MODE_UPDATE_STATS_RESET : MODE_UPDATE_STATS)
@@ -632,7 +645,7 @@ int autoloco_launch_shape(const autoloco_ctx* c, int64_t n, int32_t k, int32_t d
     if (c == nullptr || blocks == nullptr || threads == nullptr || n < 0 || n > kMaxN) return AUTOLOCO_E_INVALID;
     if (dtype != AUTOLOCO_F32 && dtype != AUTOLOCO_BF16) return AUTOLOCO_E_INVALID;
     if (k < 1 || k > AUTOLOCO_MAX_K) return AUTOLOCO_E_INVALID;
-    *blocks = blocks_for(c, n, dtype, k);
+    *blocks = fused_blocks(c, n, dtype, k);
     *threads = kBlock;
     return AUTOLOCO_OK;
 }
@@ -804,7 +817,7 @@ int autoloco_traffic_reference(autoloco_ctx* c, const autoloco_buffers* b) {
     DeviceGuard g(c->device);
     if (!g.ok) return fail(c, AUTOLOCO_E_DEVICE, "hipSetDevice failed");
     RoundArgs a = make_args(c, b);
-    const int blocks = blocks_for(c, b->n, b->replica_dtype, b->k);
+    const int blocks = fused_blocks(c, b->n, b->replica_dtype, b->k);
     int ts = timer_start(c);
     if (ts != AUTOLOCO_OK) return ts;
     hipError_t e = launch_traffic(b->replica_dtype == AUTOLOCO_BF16 ? RT_BF16 : RT_F32, b->k, blocks, c->stream, a, 0u);
@@ -1083,7 +1096,7 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
         for (int k = 0; k < b->k; ++k) na.grads[k] = b->grads[k];
         na.n = b->n;
         na.partials = c->partials;
-        nblocks = blocks_for(c, b->n, AUTOLOCO_F32, b->k, false, false);
+        nblocks = blocks_for(c, b->n, AUTOLOCO_F32, b->k, 3);
         e = launch_grad_norm(b->k, nblocks, c->stream, na);
         if (e != hipSuccess) return hip_fail(c, e, "gradient norm launch");
     }
