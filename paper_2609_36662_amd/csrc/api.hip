@@ -169,9 +169,9 @@ int reset_blocks(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k) {
 // Workgroups per worker of the AdamW update: one per compute unit in total from
 // 16M worker-parameters on, two below, split evenly over the workers' grid rows and
 // never beyond (one workgroup more than the units hold at once runs alone at the
-// end).  MI355X, plain allocations, update pass: 124M K = 4 2.50 ms at 256 against
-// 2.60 at 512, K = 8 5.11 against 5.38, K = 1 0.59 against 0.63; 5M K = 4 99 us
-// against 103, but K = 1 29.0 against 28.4; 1M alike.
+// end).  MI355X, update pass, one against two: plain allocations 124M K = 4 2.45 ms
+// against 2.60, K = 8 5.01 against 5.36, K = 1 0.58 against 0.61; buffers spread in
+// HBM 2.26 against 2.28, 4.55 against 4.63, 0.57 against 0.62; 1M alike.
 int adamw_blocks(const autoloco_ctx* ctx, int64_t n, int k) {
     int limit = ctx->grid_limit > 0 ? ctx->grid_limit : ctx->num_cus * (n >= (int64_t(16) << 20) / k ? 1 : 2);
     if (limit > kMaxBlocks) limit = kMaxBlocks;
