@@ -643,12 +643,14 @@ def bench_share(args) -> int:
     num_cus = torch.cuda.get_device_properties(dev).multi_processor_count
     R, W, RW = al.PROBE_READ, al.PROBE_WRITE, al.PROBE_READ | al.PROBE_WRITE
     refs = {
-        "payload": ([(theta, R), (rep, R), (payload, W)], al.PROBE_RUN2, args.grid or 2 * num_cus),
+        "payload": ([(theta, R), (rep, R), (payload, W)], al.PROBE_RUN2,
+                    args.grid or (1 if rdt == "f32" and n >= 1 << 28 else 2) * num_cus),
         "shard_step": ([(theta[:ns], RW), (v_shard, RW)] + [(r, R) for r in recv] + [(mean, W)], al.PROBE_RUN2,
-                       args.grid or 3 * num_cus),
-        # the reset alone runs three workgroups per compute unit
+                       args.grid or (1 if ns >= 1 << 22 else 3) * num_cus),
+        # the reset into one fp32 replica copies spans of four windows at one workgroup
+        # per compute unit; the probe has no such shape, one window at three is its best
         "reset": ([(theta, R), (rep, W)], al.PROBE_RUN1 if rdt == "f32" else al.PROBE_RUN2,
-                  args.grid or 3 * num_cus),
+                  args.grid or (2 if rdt != "f32" and n >= 100 * 1000 * 1000 else 3) * num_cus),
     }
     ref_ms = {}
     for name, (streams, shape, blocks) in refs.items():
@@ -708,8 +710,9 @@ RESET_SOURCES = [os.path.join(CSRC, f) for f in ("reset_kernels.hpp", "round_ker
 
 def reset_probe_shape(al, rdt: str, k: int) -> int:
     """The probe shape with the standalone reset's loads and stores: the runs
-    per lane its launcher picks (eight from three fp32 replicas on, one below,
-    two for bf16 replicas)."""
+    per lane its launcher picks (eight from three fp32 replicas on, two for bf16
+    replicas), one below; the copy into one large fp32 replica takes four, for
+    which the probe has no shape."""
     if rdt != "f32":
         return al.PROBE_RUN2
     return al.PROBE_RUN8 if k >= 3 else al.PROBE_RUN1
@@ -759,8 +762,8 @@ def bench_reset(args) -> int:
     torch.cuda.synchronize()
     ms_per_step = (time.perf_counter() - t0) / args.steps * 1e3
     ms = median_ms(lambda: al.autoloco_broadcast_reset(ctx, theta, reps))
-    # the reset's own pattern at its grid (three workgroups per compute unit)
-    blocks = args.grid or 3 * num_cus
+    # the reset's own pattern at its grid
+    blocks = args.grid or (2 if rdt != "f32" and k <= 2 and n >= 100 * 1000 * 1000 else 3) * num_cus
     shape = reset_probe_shape(al, rdt, k)
     try:
         ref_ms = median_ms(lambda: al.autoloco_traffic_probe(ctx, [(theta, al.PROBE_READ)] +

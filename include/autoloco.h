@@ -99,9 +99,9 @@ int autoloco_set_timing(autoloco_ctx* ctx, int enable);
  * E_DEVICE. */
 int autoloco_last_kernel_ms(autoloco_ctx* ctx, float* ms);
 /* Cap on the number of workgroups of the streaming kernels, 0..16384 (0 = the
- * default: one workgroup per compute unit from k = 5 with fp32 replicas and
- * from k = 6 with bf16, below that three, or fewer
- * if the fused kernel's register use fits fewer).  The statistics
+ * default: one workgroup per compute unit for every call with statistics; one to
+ * three without them, by k, replica type and size, or fewer if the fused
+ * kernel's register use fits fewer).  The statistics
  * are bit-identical between runs with the same n, k, replica type, device and
  * cap, and between the standalone and the fused call. */
 int autoloco_set_grid_limit(autoloco_ctx* ctx, int max_blocks);
@@ -258,8 +258,8 @@ int autoloco_outer_step_bf16(autoloco_ctx* ctx, const autoloco_buffers* bufs,
  * calls that overlap in time on one device (from several threads or streams)
  * race on the array and give wrong statistics: serialise them.
  * Errors: E_INVALID (as autoloco_outer_step, a bad device ordinal, or a launch
- * shape of more than 1,024 workgroups, which a device of more than 341
- * compute units would need below k = 8), E_ALIGN, E_ALIAS, E_DEVICE.  There is
+ * shape of more than 1,024 workgroups, which a device of more than 1,024
+ * compute units would need), E_ALIGN, E_ALIAS, E_DEVICE.  There is
  * no context, so no message is kept. */
 int autoloco_outer_step_static(int device, void* stream, const autoloco_buffers* bufs,
                                const autoloco_outer_coeffs* coeffs, uint32_t flags, double eps,

@@ -31,9 +31,8 @@ namespace {
 
 constexpr int kMaxBlocks = 16384;   // scratch sized for this many workgroups
 
-// Workgroups whose partial sums the static scratch below holds: the default
-// grid is one workgroup per compute unit from K = 5 (fp32 replicas) or 6 (bf16)
-// and three below (768 on MI355X).
+// Workgroups whose partial sums the static scratch below holds: the default grid
+// with statistics is one workgroup per compute unit (256 on MI355X).
 constexpr int kStaticBlocks = 1024;
 
 }  // namespace
