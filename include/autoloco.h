@@ -89,7 +89,8 @@ const char* autoloco_last_error(const autoloco_ctx* ctx);
 
 /* Record HIP events around the device work of every call made through ctx (on
  * the context's stream: the streaming kernel and, when the call returns sums,
- * the one-workgroup kernel that adds the per-workgroup partials after it) so
+ * the one-workgroup kernel that adds the per-workgroup partials after it, which
+ * the smallest calls leave to the host) so
  * that autoloco_last_kernel_ms() can report the device time of the most recent
  * call.  Off by default. */
 int autoloco_set_timing(autoloco_ctx* ctx, int enable);

@@ -35,6 +35,9 @@ constexpr int kMaxBlocks = 16384;   // scratch sized for this many workgroups
 // with statistics is one workgroup per compute unit (256 on MI355X).
 constexpr int kStaticBlocks = 1024;
 
+// Partial sums of a small call in host memory, per context (host_adds).
+constexpr int kHostPartials = 1024;
+
 }  // namespace
 
 // Reduction scratch of autoloco_outer_step_static on every device: per-workgroup
@@ -54,6 +57,10 @@ struct autoloco_ctx {
     double* sums = nullptr;
     double* host_sums = nullptr;
     double* host_sums_dev = nullptr;  // device view of host_sums (coherent host memory), or null
+    // partial sums of small calls that the host adds up itself: after the kMaxSums
+    // final sums in the same allocation (null where host_sums_dev is)
+    double* host_partials = nullptr;
+    double* host_partials_dev = nullptr;
     bool timing = false;
     bool timed_valid = false;
     hipEvent_t ev_start = nullptr, ev_stop = nullptr, ev_mid = nullptr;
@@ -310,24 +317,74 @@ int sums_to_host(autoloco_ctx* c, size_t count) {
     return AUTOLOCO_OK;
 }
 
+// Whether the host adds up the per-workgroup sums of a call itself: the kernel then
+// stores them in host memory, and the call is one launch instead of two.  Up to 1,024
+// of them: beyond, the stores' way over the bus costs what the launch did.  Whole call,
+// second kernel against the host: 10,007 parameters K = 2 (50 partials) 18.5 us against
+// 16.6, K = 16 (330) 24.7 against 22.9; 100,003 K = 4 (882) 19.6 against 18.4; 1M
+// K = 1 (768) 19.2 against 17.9, K = 4 (2,304) 21.8 against 22.3, K = 8 (4,352) 28.6
+// against 31.0.
+bool host_adds(const autoloco_ctx* c, int ns, int blocks) {
+    return c->host_partials_dev != nullptr && static_cast<int64_t>(ns) * blocks <= kHostPartials;
+}
+
+// Stage 2 of the reduction on the host, in finish_sums_kernel's order (thread t of nt
+// adds the workgroups t, t + nt, ...; then the exchanges of wave_sums, lane distances
+// 32, 16, 8, the half-row mirror, 1 and 2; then the wavefronts in order), so the sums
+// have that kernel's bits: partials[ns][nblocks] into sums[0..ns).
+void host_finish_sums(const double* partials, int ns, int nt, int nblocks, double* sums) {
+    for (int j = 0; j < ns; ++j) {
+        const double* p = partials + static_cast<int64_t>(j) * nblocks;
+        double total = 0.0;
+        for (int w = 0; w * 64 < nt && (w == 0 || w * 64 < nblocks); ++w) {
+            double x[64] = {};
+            for (int b = w * 64; b < nblocks; b += nt)
+                for (int i = 0; i < 64 && b + i < nblocks; ++i) x[i] += p[b + i];
+            for (int d = 32; d >= 8; d /= 2)
+                for (int i = 0; i < d; ++i) x[i] += x[i + d];
+            for (int i = 0; i < 4; ++i) x[i] += x[7 - i];
+            const double wave = (x[0] + x[1]) + (x[2] + x[3]);
+            total = w == 0 ? wave : total + wave;
+        }
+        sums[j] = total;
+    }
+}
+
+// Second stage of a call whose kernel stored its partials where host_adds said: a
+// kernel, or nothing to launch.
+int launch_stage2(autoloco_ctx* c, int ns, int nt, int blocks) {
+    if (host_adds(c, ns, blocks)) return AUTOLOCO_OK;
+    const hipError_t e = launch_finish_sums(ns, nt, blocks, c->partials, c->sums, c->stream, c->host_sums_dev);
+    return e == hipSuccess ? AUTOLOCO_OK : hip_fail(c, e, "reduction launch");
+}
+
+// Waits for the sums of that call: host_sums[0..ns).
+int wait_stage2(autoloco_ctx* c, int ns, int nt, int blocks) {
+    if (!host_adds(c, ns, blocks)) return sums_to_host(c, ns);
+    const hipError_t e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+    host_finish_sums(c->host_partials, ns, nt, blocks, c->host_sums);
+    return AUTOLOCO_OK;
+}
+
 // Launches one round kernel (timed if requested); with stats, waits for the
 // sums and fills *out.
-int run_round(autoloco_ctx* ctx, const autoloco_buffers* b, const RoundArgs& a, int mode, bool stats,
+int run_round(autoloco_ctx* ctx, const autoloco_buffers* b, RoundArgs a, int mode, bool stats,
               double eps, autoloco_stats* out) {
     const int plain = mode >= MODE_P_UPDATE ? mode - 4 : mode;   // the mode with the same outputs
     const bool reset = plain == MODE_UPDATE_RESET || plain == MODE_UPDATE_STATS_RESET;
     const int blocks = blocks_for(ctx, b->n, b->replica_dtype, b->k,
                                   round_per_cu(b->n, b->replica_dtype, b->k, stats, reset), mode >= MODE_P_UPDATE);
+    const int ns = 2 * b->k + 1;
+    if (stats && host_adds(ctx, ns, blocks)) a.partials = ctx->host_partials_dev;
     int ts = timer_start(ctx);
     if (ts != AUTOLOCO_OK) return ts;
     hipError_t e = launcher(b->replica_dtype, mode)(b->k, blocks, ctx->stream, a);
     if (e != hipSuccess) return hip_fail(ctx, e, "kernel launch");
-    if (stats && (e = launch_finish_sums(2 * b->k + 1, kBlock, blocks, ctx->partials, ctx->sums, ctx->stream,
-                                         ctx->host_sums_dev)) != hipSuccess)
-        return hip_fail(ctx, e, "reduction launch");
+    if (stats && (ts = launch_stage2(ctx, ns, kBlock, blocks)) != AUTOLOCO_OK) return ts;
     if ((ts = timer_stop(ctx)) != AUTOLOCO_OK) return ts;
     if (stats) {
-        if ((ts = sums_to_host(ctx, 2 * b->k + 1)) != AUTOLOCO_OK) return ts;
+        if ((ts = wait_stage2(ctx, ns, kBlock, blocks)) != AUTOLOCO_OK) return ts;
         finish_stats(ctx->host_sums, b->k, eps, out);
     }
     ctx->err.clear();
@@ -576,13 +633,17 @@ int autoloco_create(int device, void* stream, autoloco_ctx** out) {
     }
     bool ok = hipMalloc(&c->partials, sizeof(double) * kMaxSums * kMaxBlocks) == hipSuccess &&
               hipMalloc(&c->sums, sizeof(double) * kMaxSums) == hipSuccess &&
-              hipHostMalloc(&c->host_sums, sizeof(double) * kMaxSums, hipHostMallocMapped | hipHostMallocCoherent) ==
-                  hipSuccess;
+              hipHostMalloc(&c->host_sums, sizeof(double) * (kMaxSums + kHostPartials),
+                            hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess;
     // the reduction writes the sums to host_sums through its device view; without
     // one, they are copied
     if (ok && hipHostGetDevicePointer(reinterpret_cast<void**>(&c->host_sums_dev), c->host_sums, 0) != hipSuccess) {
         c->host_sums_dev = nullptr;
         (void)hipGetLastError();
+    }
+    if (ok && c->host_sums_dev != nullptr) {
+        c->host_partials = c->host_sums + kMaxSums;
+        c->host_partials_dev = c->host_sums_dev + kMaxSums;
     }
     ok = ok && hipMemset(c->sums, 0, sizeof(double) * kMaxSums) == hipSuccess;
     ok = ok && hipEventCreate(&c->ev_start) == hipSuccess && hipEventCreate(&c->ev_stop) == hipSuccess &&
@@ -776,16 +837,16 @@ int autoloco_outer_step_int8(autoloco_ctx* c, const autoloco_buffers* b, const a
     static const Int8Launcher table[2][2][2] = {
         {{launch_int8_f32_s0r0, launch_int8_f32_s0r1}, {launch_int8_f32_s1r0, launch_int8_f32_s1r1}},
         {{launch_int8_bf16_s0r0, launch_int8_bf16_s0r1}, {launch_int8_bf16_s1r0, launch_int8_bf16_s1r1}}};
+    const int ns = 2 * b->k + 1;
+    if (stats && host_adds(c, ns, blocks)) a.partials = c->host_partials_dev;
     int ts = timer_start(c);
     if (ts != AUTOLOCO_OK) return ts;
     hipError_t e = table[rt][stats ? 1 : 0][reset ? 1 : 0](b->k, blocks, c->stream, a);
     if (e != hipSuccess) return hip_fail(c, e, "kernel launch");
-    if (stats && (e = launch_finish_sums(2 * b->k + 1, kInt8Threads, blocks, c->partials, c->sums, c->stream,
-                                         c->host_sums_dev)) != hipSuccess)
-        return hip_fail(c, e, "reduction launch");
+    if (stats && (ts = launch_stage2(c, ns, kInt8Threads, blocks)) != AUTOLOCO_OK) return ts;
     if ((ts = timer_stop(c)) != AUTOLOCO_OK) return ts;
     if (stats) {
-        if ((ts = sums_to_host(c, 2 * b->k + 1)) != AUTOLOCO_OK) return ts;
+        if ((ts = wait_stage2(c, ns, kInt8Threads, blocks)) != AUTOLOCO_OK) return ts;
         finish_stats(c->host_sums, b->k, eps, out);
     }
     c->err.clear();

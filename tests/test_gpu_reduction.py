@@ -47,3 +47,23 @@ def test_every_sum_in_its_place(ctx, k, grid):
         al.autoloco_set_grid_limit(ctx, 0)
     payload = torch.empty(N, dtype=torch.bfloat16, device="cuda")
     assert al.autoloco_rank_payload(ctx, torch.zeros(N, device="cuda"), reps[k - 1], payload) == want[k - 1]
+
+
+# Up to 1,024 partial sums the host adds them up in the second stage's order; the call
+# without a context always launches that stage: equal bits on random inputs at one
+# workgroup, below a wavefront's 64, and on both sides of 1,024 (1,024 parameters a
+# workgroup, 2K + 1 sums).
+@pytest.mark.parametrize("k", [1, 2, 8, 16])
+def test_host_and_kernel_second_stage_agree(ctx, k):
+    most = 1024 // (2 * k + 1)
+    coeffs = al.make_coeffs(0.9, 0.7)
+    for blocks in sorted({1, 2, 31, 65, 129, most - 1, most, most + 1}):
+        n = blocks * 1024 - 5
+        g = torch.Generator(device="cuda").manual_seed(blocks)
+        theta = torch.randn(n, device="cuda", generator=g)
+        reps = [theta + torch.randn(n, device="cuda", generator=g) * 10.0 ** (i % 5 - 4) for i in range(k)]
+        momentum = torch.zeros(n, device="cuda")
+        want = al.autoloco_outer_step_static(theta.clone(), momentum.clone(), reps, coeffs, al.FUSE_STATS)
+        got = al.autoloco_outer_step(ctx, theta.clone(), momentum.clone(), reps, coeffs, al.FUSE_STATS)
+        assert got.as_dict() == want.as_dict(), blocks
+        assert al.autoloco_round_stats(ctx, theta, reps).as_dict() == want.as_dict(), blocks
