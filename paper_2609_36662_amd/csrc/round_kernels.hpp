@@ -166,7 +166,9 @@ __device__ __forceinline__ void one_param(float th, float v, const float (&r)[K]
 // Whole windows a workgroup keeps in flight (see the main loop).
 //   Statistics only, which has no stores to overlap its loads with: about 256 bytes
 //   of loads a lane, at most 8 windows.  384 to 768 bytes run alike at large sizes
-//   and slower at small ones (10M, K = 8 bf16: 41 us at 256, 51 at 768).
+//   and slower at small ones (10M, K = 8 bf16: 41 us at 256, 51 at 768).  Two windows
+//   of 15 or 16 fp32 replicas, whose one is that much already: 300M, K = 15 2.87 ms
+//   against 3.28 with one, 10M 106 us against 114.
 //   The update with statistics and without the reset of up to 4 fp32 replicas, whose
 //   one window a lane is too few loads for one workgroup a CU: about 160 bytes
 //   (124M, K = 4: 0.79 ms with one window, 0.72 with two; 0.73 at three
@@ -175,6 +177,7 @@ __device__ __forceinline__ void one_param(float th, float v, const float (&r)[K]
 template <int K, int RT, bool STATS, bool UPDATE, bool RESET>
 constexpr int windows_ahead() {
     const int bytes = RT == RT_F32 ? 16 * (K + 1) : 32 + 16 * K;
+    if (!UPDATE && RT == RT_F32 && K >= 15) return 2;
     if (!UPDATE) return bytes >= 256 ? 1 : (256 + bytes - 1) / bytes > 8 ? 8 : (256 + bytes - 1) / bytes;
     if (RT == RT_F32 && STATS && !RESET && K <= 4) return (160 + 16 * (K + 2) - 1) / (16 * (K + 2));
     return 1;
@@ -215,8 +218,9 @@ __global__ void __launch_bounds__(kBlock) round_kernel(RoundArgs a) {
     // Kernel time: BF16 payload, 124M: K = 16 1.87 ms against 2.26, K = 15 1.73 against
     // 1.92; 10M, K = 14 126 us against 165.  Without it, 10M: K = 15 131 us against 141,
     // K = 14 125 against 148; K = 16 at 30M is 1 % slower.  Below 12 the compiler's order
-    // is as fast or, at 124M and K = 9 to 11, 5 % faster.
-    constexpr bool TOGETHER = RT == RT_F32 && UPDATE && !STATS && !RESET && K >= 12;
+    // is as fast or, at 124M and K = 9 to 11, 5 % faster.  The same for a single window of
+    // the statistics alone of 15 or 16 (10,000 parameters, K = 15: 7.4 us against 8.2).
+    constexpr bool TOGETHER = RT == RT_F32 && (UPDATE ? !STATS && !RESET && K >= 12 : K >= 15);
     struct Window {
         f32x4 t[R], v[UPDATE ? R : 1];
         f32x4 rf[RAW ? 1 : K][RAW ? 1 : R];

@@ -30,6 +30,8 @@ def _round(k, stats, update, reset, payload=0):
 KERNELS = []
 # the plain update of many fp32 replicas, with the mean as it is and through the BF16 payload
 KERNELS += [_round(k, 0, 1, 0, p) for k in (12, 13, 14, 15, 16) for p in (0, 1)]
+# the statistics alone of the most fp32 replicas
+KERNELS += [_round(k, 1, 0, 0) for k in (15, 16)]
 
 
 def _hipcc():
