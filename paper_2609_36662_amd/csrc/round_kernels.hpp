@@ -221,6 +221,15 @@ __global__ void __launch_bounds__(kBlock) round_kernel(RoundArgs a) {
     // is as fast or, at 124M and K = 9 to 11, 5 % faster.  The same for a single window of
     // the statistics alone of 15 or 16 (10,000 parameters, K = 15: 7.4 us against 8.2).
     constexpr bool TOGETHER = RT == RT_F32 && (UPDATE ? !STATS && !RESET && K >= 12 : K >= 15);
+    // BF16 payload: the received mean goes out after theta and the momentum.  Stored
+    // first, the wait for the last load of the window, the momentum's, was also a wait
+    // for that store, and the window's other stores came only then.  (Fused with the
+    // mean: fp32, 30M K = 2 171 us against 201, 124M K = 8 1.89 ms against 1.92; bf16, 30M
+    // K = 7 248 us against 263.  Plain update of bf16 replicas: 124M K = 9 0.75 ms against
+    // 0.80.)  First elsewhere, where the compiler then orders the loads better: 5 and 6
+    // fp32 replicas fused run 1-3 % faster so at 30M to 124M, their update with statistics
+    // or reset alone up to 10 %, and the rest alike.
+    constexpr bool PAYLOAD_LAST = RT == RT_F32 ? STATS && RESET && K <= 8 && K != 5 && K != 6 : STATS == RESET && K >= 7;
     struct Window {
         f32x4 t[R], v[UPDATE ? R : 1];
         f32x4 rf[RAW ? 1 : K][RAW ? 1 : R];
@@ -295,15 +304,16 @@ __global__ void __launch_bounds__(kBlock) round_kernel(RoundArgs a) {
         for (int h = 0; h < R; ++h) {
             if (h == 1 && !ok1) continue;
             const uint32_t fo = (h * kBlock + threadIdx.x) * 16u;
-            if constexpr (BF16P) {
-                // 2 bytes per parameter: 8 per quad
+            auto store_payload = [&] {   // 2 bytes per parameter: 8 per quad
                 if (a.payload != nullptr)
                     st_u2_at(a.payload + wb, fo / 2, u32x2r{pb[4 * h] | pb[4 * h + 1] << 16,
                                                             pb[4 * h + 2] | pb[4 * h + 3] << 16});
-            }
+            };
+            if constexpr (BF16P && !PAYLOAD_LAST) store_payload();
             const f32x4 o = {th_new[4 * h], th_new[4 * h + 1], th_new[4 * h + 2], th_new[4 * h + 3]};
             st_f4_at(th_w, fo, o);
             st_f4_at(mo_w, fo, f32x4{v_new[4 * h], v_new[4 * h + 1], v_new[4 * h + 2], v_new[4 * h + 3]});
+            if constexpr (BF16P && PAYLOAD_LAST) store_payload();
             if constexpr (RESET) {
                 if constexpr (RT == RT_F32) {
 #pragma unroll
