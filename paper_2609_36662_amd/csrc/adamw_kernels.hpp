@@ -59,7 +59,11 @@ struct AdamWArgs {
 // Windows of its grid-stride sequence a thread loads before it adds any of them
 // up (in that order, so every per-thread sum is what one window at a time gives):
 // one worker's stream alone keeps too few bytes in flight at three workgroups a CU.
-// (124M: K = 1 77 us against 109; from K = 3 on nothing is gained.)
+// (124M: K = 1 77 us against 109; from K = 3 on nothing is gained.)  The loads of a
+// window of all workers go out together: left alone, the compiler puts more and more
+// of them behind the first sums from K = 11 on, one at a time at K = 16 (whole step,
+// 124M: K = 16 11.8 ms against 12.5, K = 15 11.1 against 11.7; 10,000 parameters
+// 13.2 us against 18.9 and 17.0).
 template <int K>
 constexpr int norm_unroll() {
     return K == 1 ? 4 : K == 2 ? 2 : 1;
@@ -95,8 +99,12 @@ __global__ void __launch_bounds__(kBlock) grad_norm_kernel(GradNormArgs a) {
         }
     }
     for (; i < nvec; i += stride) {
+        f32x4 g[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) add(k, ld_f4(a.grads[k] + 4 * i));
+        for (int k = 0; k < K; ++k) g[k] = ld_f4(a.grads[k] + 4 * i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) add(k, g[k]);
     }
     if (blockIdx.x == 0 && threadIdx.x < (a.n & 3)) {
         const int64_t j = nvec * 4 + threadIdx.x;

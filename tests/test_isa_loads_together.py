@@ -32,6 +32,9 @@ KERNELS = []
 KERNELS += [_round(k, 0, 1, 0, p) for k in (12, 13, 14, 15, 16) for p in (0, 1)]
 # the statistics alone of the most fp32 replicas
 KERNELS += [_round(k, 1, 0, 0) for k in (15, 16)]
+# AdamW's norm pass: every worker's gradient
+KERNELS += [(f"grad_norm_kernel<{k}>(GradNormArgs)", f"_ZN8autoloco16grad_norm_kernelILi{k}EEEvNS_12GradNormArgsE", k)
+            for k in (3, 8, 11, 12, 13, 14, 15, 16)]
 
 
 def _hipcc():
