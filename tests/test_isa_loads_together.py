@@ -35,6 +35,8 @@ KERNELS += [_round(k, 1, 0, 0) for k in (15, 16)]
 # AdamW's norm pass: every worker's gradient
 KERNELS += [(f"grad_norm_kernel<{k}>(GradNormArgs)", f"_ZN8autoloco16grad_norm_kernelILi{k}EEEvNS_12GradNormArgsE", k)
             for k in (3, 8, 11, 12, 13, 14, 15, 16)]
+# the shard step with one payload: two runs of theta, momentum and payload
+KERNELS += [("shard_step_kernel<1>(ShardArgs)", "_ZN8autoloco17shard_step_kernelILi1EEEvNS_9ShardArgsE", 3)]
 
 
 def _hipcc():
@@ -76,7 +78,7 @@ def test_no_wait_between_the_loads_of_a_window(asm, symbol, loads):
     for block in _blocks(asm, symbol):
         runs, run = [], 0
         for line in block:
-            if line.startswith("global_load_dwordx4"):
+            if line.startswith("global_load_dwordx"):
                 run += 1
             elif run and line.startswith("s_waitcnt") and "vmcnt(" in line:
                 runs.append(run)
