@@ -1116,9 +1116,11 @@ int autoloco_shard_step(autoloco_ctx* c, const autoloco_shard_buffers* b, const 
     a.partials = c->partials;
     // One workgroup a CU from 4M parameters on, three below (MI355X, 1.1B / 8 K = 8
     // 720-795 us at 256 against 833 at 768, 275M K = 1 0.82 ms against 0.95, 25M K = 16
-    // 206 us against 216; 7.5M alike; 1.9M K = 16 24.2 us against 22.9).
-    const int blocks = blocks8(c, b->n, b->n >= (int64_t(4) << 20) ? 1 : 3);
+    // 206 us against 216; 7.5M alike; 1.9M K = 16 24.2 us against 22.9).  From 12M with
+    // four or five payloads (K = 4: 5M 28.9 us at 256 against 28.1, 8M 40.8 against 39.0;
+    // 16M 4 % faster, 124M 10 %).
     const int k = b->k;
+    const int blocks = blocks8(c, b->n, b->n >= (int64_t(k == 4 || k == 5 ? 12 : 4) << 20) ? 1 : 3);
     return run_one_sum(c, [&] { return launch_shard_step(k, blocks, c->stream, a); }, blocks, sq_mean);
 }
 
