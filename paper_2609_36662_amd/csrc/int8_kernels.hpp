@@ -291,13 +291,13 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
             (void __attribute__((address_space(3)))*)(lds_pf + vec + wave * 64), 16, 0, 2);
     };
     // Issues the direct loads of full block b: theta's, and the replicas'.
-    auto pf_theta = [&](int64_t b) {
+    auto pf_theta = [&](int64_t b, uint32_t lanes) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) to_lds(fbase(a.theta, b, g), fo, g * NT);
+        for (int g = 0; g < G; ++g) to_lds(fbase(a.theta, b, g), fo & lanes, g * NT);
     };
-    auto pf_replicas = [&](int64_t b) {
+    auto pf_replicas = [&](int64_t b, uint32_t lanes) {
         if constexpr (RT == RT_F32) {
-            uint32_t o = fo;
+            uint32_t o = fo & lanes;
             asm volatile("" : "+v"(o));   // no per-lane sums kept across the loop
 #pragma unroll
             for (int k = 0; k < LK; ++k)
@@ -305,21 +305,29 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
                 for (int g = 0; g < G; ++g) to_lds(fbase(a.replicas[k], b, g), o, G * NT + k * RV + g * NT);
         } else {
             // lanes 0..31 the wave's first run (512 B), lanes 32..63 its second
-            uint32_t ro = (lane >> 5) * kCodecBlock + wave * 512u + (lane & 31) * 16u;
+            uint32_t ro = ((lane >> 5) * kCodecBlock + wave * 512u + (lane & 31) * 16u) & lanes;
             asm volatile("" : "+v"(ro));
 #pragma unroll
             for (int k = 0; k < LK; ++k) to_lds(bbase(a.replicas[k], b, 0), ro, G * NT + k * RV);
         }
     };
     f32x4 nx[RK > 0 ? RK : 1][G];   // the next block's vectors of workers LK..K-1
-    auto reg_issue = [&](int64_t b, int k) {
+    auto reg_issue = [&](int64_t b, uint32_t lanes, int k) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) nx[k - LK][g] = ld_f4_at(fbase(a.replicas[k], b, g), fo);
+        for (int g = 0; g < G; ++g) nx[k - LK][g] = ld_f4_at(fbase(a.replicas[k], b, g), fo & lanes);
     };
 
     auto body = [&](int64_t blk, auto full_c) {
         constexpr bool FULL = decltype(full_c)::value;
-        const int64_t nb = blk + gridDim.x < nfull ? blk + gridDim.x : blk;
+        // The workgroup's next block.  On its last one the loads are issued all the same
+        // (a branch around them takes up to 30 registers more, and K = 15 and 16 spill),
+        // but all lanes of a load then read the same 16 bytes, the first of this block's
+        // run, and nothing uses them: this block read once more cost a sixth of the call
+        // where a workgroup has one block (1M, K = 12 fp32 with the reset and without
+        // statistics: 28 us against 33; 4M 97 against 104).
+        const bool more = blk + gridDim.x < nfull;
+        const int64_t nb = more ? blk + gridDim.x : blk;
+        const uint32_t lanes = more ? ~0u : 0u;
         int64_t off[G];
         int valid[G];
 #pragma unroll
@@ -371,12 +379,10 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
                 }
             }
             // every LDS read of this block has returned before the next block's
-            // direct loads overwrite the pieces (on the workgroup's last block this
-            // block again, so that every iteration issues the same instructions;
-            // those values are not used)
+            // direct loads overwrite the pieces
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if constexpr (KEEP_THETA) pf_theta(nb);
-            pf_replicas(nb);
+            if constexpr (KEEP_THETA) pf_theta(nb, lanes);
+            pf_replicas(nb, lanes);
         } else {
 #pragma unroll
             for (int g = 0; g < G; ++g)
@@ -481,7 +487,7 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
                 for (int e = 0; e < W; ++e) th[g * W + e] = t4[e];
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            pf_theta(nb);
+            pf_theta(nb, lanes);
         }
 
         // deviations from the aggregate; a worker's pseudo-gradients are not used
@@ -504,7 +510,7 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
             if constexpr (FULL && RK > 0) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (4 * j + i >= LK && 4 * j + i < K) reg_issue(nb, 4 * j + i);
+                    if (4 * j + i >= LK && 4 * j + i < K) reg_issue(nb, lanes, 4 * j + i);
             }
         }
         if constexpr (STATS) {
@@ -581,14 +587,14 @@ __global__ void __launch_bounds__(kInt8Threads) int8_round_kernel(Int8Args a) {
     };
 
     if (blockIdx.x < nfull) {
-        pf_theta(blockIdx.x);
-        pf_replicas(blockIdx.x);
+        pf_theta(blockIdx.x, ~0u);
+        pf_replicas(blockIdx.x, ~0u);
 #pragma unroll
-        for (int k = LK; k < K; ++k) reg_issue(blockIdx.x, k);
+        for (int k = LK; k < K; ++k) reg_issue(blockIdx.x, ~0u, k);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the first block's pieces are in LDS
     for (int64_t blk = blockIdx.x; blk < nfull; blk += gridDim.x) body(blk, BoolC<true>{});
-    // the last iteration's direct loads (a re-read, unused) land before anything
+    // the last iteration's direct loads (unused) land before anything
     // else uses this workgroup's LDS or the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // the shorter last block belongs to the workgroup the grid stride gives it
