@@ -1258,10 +1258,14 @@ hipError_t reset_k(int rt, int blocks, hipStream_t s, const RoundArgs& a) {
         hipLaunchKernelGGL((reset_kernel<K, RT_BF16, 2>), dim3(blocks), dim3(kBlock), 0, s, a);
     else if constexpr (K >= 3)
         hipLaunchKernelGGL((reset_kernel<K, RT_F32, 8>), dim3(blocks), dim3(kBlock), 0, s, a);
-    else if (K == 1 && reset_span4(a.n))
-        hipLaunchKernelGGL((reset_kernel<K, RT_F32, 4>), dim3(blocks), dim3(kBlock), 0, s, a);
-    else
+    else {
+        if constexpr (K == 1)
+            if (reset_span4(a.n)) {
+                hipLaunchKernelGGL((reset_kernel<K, RT_F32, 4>), dim3(blocks), dim3(kBlock), 0, s, a);
+                return hipGetLastError();
+            }
         hipLaunchKernelGGL((reset_kernel<K, RT_F32, 1>), dim3(blocks), dim3(kBlock), 0, s, a);
+    }
     return hipGetLastError();
 }
 }  // namespace

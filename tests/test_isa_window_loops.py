@@ -23,11 +23,13 @@ CSRC = os.path.join(ROOT, "paper_2609_36662_amd", "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 
 # (symbol, loads of one whole window): the spans the reset launcher picks
-# (one window for one fp32 replica, eight from three on, two for bf16), the
-# payload kernel (theta and an fp32 replica, two runs) and the shard step
-# (theta and v in place plus 8 bf16 payload shards, two runs).
+# (one window for one fp32 replica, or four from 4M parameters on, eight from
+# three replicas on, two for bf16), the payload kernel (theta and an fp32 replica,
+# two runs) and the shard step (theta and v in place plus 8 bf16 payload shards,
+# two runs).
 KERNELS = [
     ("_ZN8autoloco12reset_kernelILi1ELi0ELi1EEEvNS_9RoundArgsE", 1),
+    ("_ZN8autoloco12reset_kernelILi1ELi0ELi4EEEvNS_9RoundArgsE", 4),
     ("_ZN8autoloco12reset_kernelILi3ELi0ELi8EEEvNS_9RoundArgsE", 8),
     ("_ZN8autoloco12reset_kernelILi8ELi0ELi8EEEvNS_9RoundArgsE", 8),
     ("_ZN8autoloco12reset_kernelILi8ELi1ELi2EEEvNS_9RoundArgsE", 2),
@@ -40,6 +42,7 @@ SOURCE = """
 #include "shard_kernels.hpp"
 namespace autoloco {
 template __global__ void reset_kernel<1, RT_F32, 1>(RoundArgs);
+template __global__ void reset_kernel<1, RT_F32, 4>(RoundArgs);
 template __global__ void reset_kernel<3, RT_F32, 8>(RoundArgs);
 template __global__ void reset_kernel<8, RT_F32, 8>(RoundArgs);
 template __global__ void reset_kernel<8, RT_BF16, 2>(RoundArgs);
