@@ -646,7 +646,7 @@ def bench_share(args) -> int:
         "payload": ([(theta, R), (rep, R), (payload, W)], al.PROBE_RUN2,
                     args.grid or (1 if rdt == "f32" and n >= 1 << 28 else 2) * num_cus),
         "shard_step": ([(theta[:ns], RW), (v_shard, RW)] + [(r, R) for r in recv] + [(mean, W)], al.PROBE_RUN2,
-                       args.grid or (1 if ns >= 1 << 22 else 3) * num_cus),
+                       args.grid or (1 if ns >= (12 if k in (4, 5) else 4) << 20 else 3) * num_cus),
         # the reset into one fp32 replica copies spans of four windows at one workgroup
         # per compute unit; the probe has no such shape, one window at three is its best
         "reset": ([(theta, R), (rep, W)], al.PROBE_RUN1 if rdt == "f32" else al.PROBE_RUN2,

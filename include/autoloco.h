@@ -100,14 +100,22 @@ int autoloco_set_timing(autoloco_ctx* ctx, int enable);
  * E_DEVICE. */
 int autoloco_last_kernel_ms(autoloco_ctx* ctx, float* ms);
 /* Cap on the number of workgroups of the streaming kernels, 0..16384 (0 = the
- * default: one workgroup per compute unit for every call with statistics; one to
- * three without them, by k, replica type and size, or fewer if the fused
- * kernel's register use fits fewer).  The statistics
- * are bit-identical between runs with the same n, k, replica type, device and
- * cap, and between the standalone and the fused call. */
+ * defaults.  The round and its statistics: one workgroup per compute unit with
+ * statistics; one to three without them, by k, replica type and size, or fewer if
+ * the fused kernel's register use fits fewer.  The INT8 round: one.  The worker
+ * payload: two, or one for large fp32 replicas.  The shard step: three, or one from
+ * 4M parameters on, 12M with four or five payloads.  The reset: three, or fewer into
+ * one or two replicas of large models.  AdamW: up to three for the norms, one or two
+ * for the update).  The round's statistics are bit-identical between runs with the
+ * same n, k, replica type, device and cap, and between the standalone and the fused
+ * call. */
 int autoloco_set_grid_limit(autoloco_ctx* ctx, int max_blocks);
-/* Workgroups and threads per workgroup a round over n parameters with k
- * replicas of the given type uses. */
+/* Workgroups and threads per workgroup of the calls with statistics over n
+ * parameters with k replicas of the given type (the round, fused or not, with the
+ * BF16 payload or without, and the standalone statistics).  A round without
+ * statistics may use up to three times as many workgroups, and the INT8 round has a
+ * shape of its own: one workgroup of 512 threads per block of 4,096 parameters, up
+ * to one per compute unit. */
 int autoloco_launch_shape(const autoloco_ctx* ctx, int64_t n, int32_t k, int32_t replica_dtype,
                           int32_t* blocks, int32_t* threads);
 

@@ -289,6 +289,8 @@ def autoloco_set_grid_limit(ctx: Context, max_blocks: int) -> None:
 
 
 def autoloco_launch_shape(ctx: Context, n: int, k: int, replica_dtype: int = F32):
+    """Workgroups and threads per workgroup of the round's calls with statistics (rounds
+    without them may use more workgroups; the INT8 round has a shape of its own)."""
     b, t = C.c_int32(), C.c_int32()
     _check(lib().autoloco_launch_shape(ctx.handle, int(n), int(k), int(replica_dtype), C.byref(b), C.byref(t)),
            "autoloco_launch_shape", ctx)

@@ -210,7 +210,11 @@ __global__ void __launch_bounds__(kBlock) adamw_kernel(AdamWArgs a) {
     // Many windows a workgroup: the next one is loaded before this one is worked on
     // (one workgroup a CU, update pass: 124M K = 4 2.45 ms against 2.53 without, K = 8
     // 5.01 against 5.15; on buffers spread in HBM 2.26 against 2.30 and 4.55 against
-    // 4.65).  Not with few, where it gains nothing (1M, K = 4: 24.8 us against 24.2).
+    // 4.65; whole step on the same buffers 1-5 % at every K from 30M to 200M).  Not with
+    // few, where it gains nothing (1M, K = 4: 24.8 us against 24.2).  The loop's waits
+    // cover the stores of the window before; two windows in turn, whose waits do not, are
+    // slower (30M: K = 4 753 us against 644, K = 8 1.44 ms against 1.28; 124M K = 4 2.81
+    // ms against 2.65): with more in flight the memory runs worse.
     if (nw >= 16 * (int64_t)gridDim.x && i >= 0) {
         Quad x = load(i);
         for (; i >= stride; i -= stride) {

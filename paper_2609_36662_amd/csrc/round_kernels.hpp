@@ -19,10 +19,10 @@
 // added in fp32 and then into per-lane fp64 running sums.  The 2K+1 sums are
 // reduced deterministically: halving exchanges in a wavefront, then the waves of the
 // workgroup in order through LDS into one partial per workgroup (a plain
-// store), then a one-workgroup kernel launched after this one on the same
-// stream adds the partials in workgroup order.  With the grid fixed, every
-// run adds the same numbers in the same order, so the statistics are
-// bit-identical between runs.
+// store), then a second stage adds the partials in a fixed order: a one-workgroup
+// kernel launched after this one on the same stream, or for the smallest calls the
+// host, in that kernel's order.  With the grid fixed, every run adds the same
+// numbers in the same order, so the statistics are bit-identical between runs.
 #pragma once
 
 #include <hip/hip_runtime.h>
