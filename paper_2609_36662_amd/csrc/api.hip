@@ -128,8 +128,10 @@ int check_device_ptr(autoloco_ctx* ctx, uintptr_t p, const char* name) {
 //     against 0.55), but for the statistics alone of one fp32 replica, which lose 1-3 %
 //     from 60M on (1.1B 1.27 ms against 1.24; 12, 14 or 20 windows in flight instead of 8
 //     do not change that) and keep the grid for the sums' order;
-//   every mode with statistics from 10,000 to 4M parameters, K = 1 to 4: 2-10 % faster
-//     at 1M and 4M, the second stage included.
+//   1M to 4M, K = 1 to 4, the same kernels at one and at three: 0.98-1.36 times as fast at
+//     one in nearly every mode with statistics (1M fp32 K = 4 fused 15.9 us against 16.6),
+//     but 0.92-0.96 for the statistics alone of two or three fp32 replicas (1M K = 2
+//     11.6 us against 10.6) and 0.93 fused at 1M with three or four bf16 ones.
 // Without statistics: one for bf16 replicas from 16M parameters on (30M K = 4 +5 %; 4M
 // K = 4 26.8 us against 25.6) and for the reset of fp32 ones from 8M replica
 // parameters on (4M K = 4 43 us against 49; 1M K = 1 9.0 against 8.5), three for the
