@@ -105,8 +105,8 @@ int autoloco_last_kernel_ms(autoloco_ctx* ctx, float* ms);
  * the fused kernel's register use fits fewer.  The INT8 round: one.  The worker
  * payload: two, or one for large fp32 replicas.  The shard step: three, or one from
  * 4M parameters on, 12M with four or five payloads.  The reset: three, or fewer into
- * one or two replicas of large models.  AdamW: up to three for the norms, one or two
- * for the update).  The round's statistics are bit-identical between runs with the
+ * one or two replicas of large models and into nine bf16 or fourteen fp32 and more.
+ * AdamW: two or three for the norms, one or two for the update).  The round's statistics are bit-identical between runs with the
  * same n, k, replica type, device and cap, and between the standalone and the fused
  * call. */
 int autoloco_set_grid_limit(autoloco_ctx* ctx, int max_blocks);

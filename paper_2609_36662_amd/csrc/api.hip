@@ -145,13 +145,10 @@ int round_per_cu(int64_t n, int32_t dtype, int k, bool stats, bool reset) {
 }
 
 // Workgroups of a kernel that takes four fp32 or eight bf16 parameters a lane, per_cu
-// a compute unit or fewer if the fused kernel's registers fit fewer.
-int blocks_for(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k, int per_cu, bool bf16p = false) {
+// a compute unit.
+int grid_at(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int per_cu) {
     const int64_t v = dtype == AUTOLOCO_BF16 ? 8 : 4;
     const int64_t nvec = n / v;
-    const int fit = (bf16p ? ctx->occupancy_bf16p : ctx->occupancy)[dtype == AUTOLOCO_BF16 ? 1 : 0][k];
-    if (per_cu > fit) per_cu = fit;
-    if (per_cu < 1) per_cu = 1;
     int limit = ctx->grid_limit > 0 ? ctx->grid_limit : ctx->num_cus * per_cu;
     if (limit > kMaxBlocks) limit = kMaxBlocks;
     int64_t want = (nvec + kBlock - 1) / kBlock;
@@ -159,18 +156,37 @@ int blocks_for(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k, int per
     return static_cast<int>(want < limit ? want : limit);
 }
 
+// The same for the round's modes: fewer if the fused kernel's registers fit fewer.
+int blocks_for(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k, int per_cu, bool bf16p = false) {
+    const int fit = (bf16p ? ctx->occupancy_bf16p : ctx->occupancy)[dtype == AUTOLOCO_BF16 ? 1 : 0][k];
+    if (per_cu > fit) per_cu = fit;
+    return grid_at(ctx, n, dtype, per_cu < 1 ? 1 : per_cu);
+}
+
+// Workgroups per compute unit of the reset and of AdamW's norm pass, which have no
+// statistics to keep in step with the round's: three, two from 9 bf16 or 14 fp32
+// replicas on, one from 14 bf16 ones on.  A rule of their own: taken from the fused
+// kernel's occupancy, the reset of 8 bf16 replicas fell from three to two when that
+// kernel's registers went from 166 to 170 (1.1B 4.44 ms against 3.96, 400M 1.83 against
+// 1.63, 10M alike).  9 and 10 bf16 replicas run 8-14 % faster at three from 400M on and
+// 9 5 % slower at 10M; 14 to 16 up to 8 % slower at 10M; fp32 ones alike.
+int copy_per_cu(int32_t dtype, int k) {
+    if (dtype == AUTOLOCO_BF16) return k <= 8 ? 3 : k <= 13 ? 2 : 1;
+    return k <= 13 ? 3 : 2;
+}
+
 // Grid of the fused round (update, statistics and reset).
 int fused_blocks(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k) {
     return blocks_for(ctx, n, dtype, k, round_per_cu(n, dtype, k, true, true));
 }
 
-// Grid of the standalone reset: three workgroups per compute unit, except the
+// Grid of the standalone reset: copy_per_cu workgroups per compute unit, except the
 // copy into one fp32 replica in spans of four windows (reset_span4), one workgroup
 // per compute unit, and one or two bf16 replicas from 100M parameters on, two
 // (MI355X: 1.1B K = 1 1.10 ms at 512 against 1.20 at 768, K = 2 1.57-1.66 against
 // 1.65; 400M K = 1 388 us against 406; 30M 32.7 against 31.7).
 int reset_blocks(const autoloco_ctx* ctx, int64_t n, int32_t dtype, int k) {
-    const int blocks = blocks_for(ctx, n, dtype, k, 3);
+    const int blocks = grid_at(ctx, n, dtype, copy_per_cu(dtype, k));
     if (ctx->grid_limit > 0) return blocks;
     const bool bf16 = dtype == AUTOLOCO_BF16;
     const int most = !bf16 && k == 1 && reset_span4(n)            ? ctx->num_cus
@@ -1143,7 +1159,7 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
         for (int k = 0; k < b->k; ++k) na.grads[k] = b->grads[k];
         na.n = b->n;
         na.partials = c->partials;
-        nblocks = blocks_for(c, b->n, AUTOLOCO_F32, b->k, 3);
+        nblocks = grid_at(c, b->n, AUTOLOCO_F32, copy_per_cu(AUTOLOCO_F32, b->k));
         e = launch_grad_norm(b->k, nblocks, c->stream, na);
         if (e != hipSuccess) return hip_fail(c, e, "gradient norm launch");
     }
