@@ -1150,6 +1150,7 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
     if (!g.ok) return fail(c, AUTOLOCO_E_DEVICE, "hipSetDevice failed");
     const bool norm_pass = clip || out != nullptr;
     int nblocks = 0;
+    bool sums_ready = false;   // the norms' sums are in c->sums already
     int ts = timer_start(c);
     if (ts != AUTOLOCO_OK) return ts;
     hipError_t e;
@@ -1162,6 +1163,15 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
         nblocks = grid_at(c, b->n, AUTOLOCO_F32, copy_per_cu(AUTOLOCO_F32, b->k));
         e = launch_grad_norm(b->k, nblocks, c->stream, na);
         if (e != hipSuccess) return hip_fail(c, e, "gradient norm launch");
+        // A grid cap above the default: so many partials cost the update's workgroups, which
+        // all add them up, more than a kernel between the passes (10M, K = 1, whole step: at
+        // a cap of 16,384 98.6 us against 72.1, at 4,096 71.9 against 68.5; at 1,024 66.3
+        // against 69.9).
+        if (nblocks > 1024) {
+            e = launch_finish_sums(b->k, kBlock, nblocks, c->partials, c->sums, c->stream);
+            if (e != hipSuccess) return hip_fail(c, e, "reduction launch");
+            sums_ready = true;
+        }
     }
     if (c->timing && (e = hipEventRecord(c->ev_mid, c->stream)) != hipSuccess) return hip_fail(c, e, "hipEventRecord");
     AdamWArgs a;
@@ -1174,10 +1184,12 @@ int autoloco_inner_adamw(autoloco_ctx* c, const autoloco_adamw_buffers* b, const
         a.copy[k] = static_cast<uint16_t*>(b->model_bf16[k]);
     }
     a.n = b->n;
-    a.partials = norm_pass ? c->partials : nullptr;
-    a.nblocks = nblocks;
+    // with the sums ready, one "partial" a worker, and the kernel's own copy of the sum
+    // goes where nothing reads it
+    a.partials = !norm_pass ? nullptr : sums_ready ? c->sums : c->partials;
+    a.nblocks = sums_ready ? 1 : nblocks;
     a.max_norm = co->max_grad_norm;
-    a.sums = c->sums;
+    a.sums = sums_ready ? c->partials : c->sums;
     a.host_sums = c->host_sums_dev;
     a.decay = static_cast<float>(1.0 - co->lr * co->weight_decay);
     a.beta1 = static_cast<float>(co->beta1);
