@@ -183,6 +183,14 @@ constexpr int windows_ahead() {
     return 1;
 }
 
+// Workgroups up to which windows are kept in flight: one a compute unit for the update,
+// three for the statistics alone.  Above (a caller's grid cap) there are waves enough,
+// and with several windows each the memory runs worse: 124M fp32 at 1,024 workgroups,
+// one window against several, statistics alone K = 1 145 us against 189, K = 8 0.64 ms
+// against 0.80 (but K = 2 310 us against 276, and 251 against 293 at 2,048), the update
+// with them K = 1 to 4 7-11 % faster.
+constexpr unsigned ahead_grid(bool update) { return update ? 256 : 768; }
+
 // ------------------------------------------------------------ round kernel --
 template <int K, int RT, bool STATS, bool UPDATE, bool RESET, bool BF16P = false>
 __global__ void __launch_bounds__(kBlock) round_kernel(RoundArgs a) {
@@ -332,7 +340,7 @@ __global__ void __launch_bounds__(kBlock) round_kernel(RoundArgs a) {
     constexpr int U = windows_ahead<K, RT, STATS, UPDATE, RESET>();
     int64_t qb = (int64_t)blockIdx.x * kBlock * R;
     if constexpr (U > 1) {
-        if (qb + (U - 1) * qstride + kBlock * R <= nq) {
+        if (gridDim.x <= ahead_grid(UPDATE) && qb + (U - 1) * qstride + kBlock * R <= nq) {
             Window w[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) load(w[u], qb + u * qstride, true);
